@@ -1546,6 +1546,7 @@ int run_measured(qw_ctx *ctx, uint32_t n, std::vector<MeasTask> &mt) {
             std::vector<uint64_t> qs(M);
             std::vector<uint32_t> tfirst(M), tcount(M);
             std::vector<MeasDec> dec;
+            uint32_t bin_blocks = 1;   // joint: workgroups of the bin sums
             for (uint32_t i = 0; i < M; ++i) {
                 MeasTask &t = mt[who[i]];
                 ptrs[i] = t.dst;
@@ -1554,6 +1555,7 @@ int run_measured(qw_ctx *ctx, uint32_t n, std::vector<MeasTask> &mt) {
                 qs[i] = C ? (msk >> C) : (uint64_t)t.cluster[0].q0;
                 tfirst[i] = (uint32_t)dec.size();
                 tcount[i] = (uint32_t)t.cluster.size();
+                if (C) bin_blocks = std::max(bin_blocks, joint_blocks(n - joint_chunk_bits(C), tcount[i]));
                 // bin bit of each measurement at its turn: its rank among the
                 // qubits still open (ascending), the decided ones removed
                 std::vector<uint32_t> alive;
@@ -1601,8 +1603,8 @@ int run_measured(qw_ctx *ctx, uint32_t n, std::vector<MeasTask> &mt) {
                     ? launch_measure_sums(ctx->stream, reinterpret_cast<const float2 *const *>(ub + o_ptr),
                                           reinterpret_cast<const uint32_t *>(ub + o_q), M, n, part, dout)
                     : launch_joint_masses(ctx->stream, reinterpret_cast<const float2 *const *>(ub + o_ptr),
-                                          reinterpret_cast<const uint64_t *>(ub + o_q), M, n, C, part,
-                                          kStride, dout);
+                                          reinterpret_cast<const uint64_t *>(ub + o_q), M, n, C, bin_blocks,
+                                          part, kStride, dout);
                 if (er != hipSuccess) return hip_fail(ctx, er, "measure launch");
                 er = launch_meas_decide(ctx->stream, reinterpret_cast<const uint32_t *>(ub + o_tf),
                                         reinterpret_cast<const uint32_t *>(ub + o_tc),

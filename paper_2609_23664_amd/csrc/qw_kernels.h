@@ -37,18 +37,27 @@ hipError_t launch_expect_finalize(hipStream_t st, const double *part, const doub
 // of slot pointers). csum/cpre: n_slots * chunks doubles; total: n_slots.
 // Measurement sums (FP64, fixed order) of n_slots states: out[2 s] = sum of
 // |psi_i|^2, out[2 s + 1] = the same over indices with bit qubit[s] set.
-// slots and qubit are device arrays; part holds 2 * n_slots * 2^(n - 14)
-// doubles (2 * n_slots for n <= 14).
+// slots and qubit are device arrays; part holds 2 * n_slots * 2^(n - 12)
+// doubles (2 * n_slots for n <= 12).
 hipError_t launch_measure_sums(hipStream_t st, const float2 *const *slots, const uint32_t *qubit,
                                uint32_t n_slots, uint32_t n, double *part, double *out);
 // Joint measurement masses of n_slots states whose measured qubits are all
 // >= C (8 <= C <= 14): out[s * bin_stride + b] = FP64 mass of outcome bin b
 // (measured bits of slot s in ascending qubit order), summed in a fixed
 // order. mq[s] = measured-qubit mask >> C (device); csum holds
-// n_slots * 2^(n - C) doubles.
+// n_slots * 2^(n - joint_chunk_bits(C)) doubles; max_blocks = the largest
+// joint_blocks(n - joint_chunk_bits(C), measured qubits) of the slots.
 hipError_t launch_joint_masses(hipStream_t st, const float2 *const *slots, const uint64_t *mq,
-                               uint32_t n_slots, uint32_t n, uint32_t C, double *csum,
-                               uint32_t bin_stride, double *out);
+                               uint32_t n_slots, uint32_t n, uint32_t C, uint32_t max_blocks,
+                               double *csum, uint32_t bin_stride, double *out);
+// Amplitudes of one chunk sum (log2): a wave's 8 loads of 16 bytes a lane at
+// most, within the lowest measured qubit.
+constexpr uint32_t joint_chunk_bits(uint32_t C) { return C < 10 ? C : 10; }
+// Workgroups that add one slot's 2^chunks_log2 chunk sums into 2^k bins: one
+// per bin of 256 or more chunks, else one per 256 chunks.
+constexpr uint32_t joint_blocks(uint32_t chunks_log2, uint32_t k) {
+    return chunks_log2 - k >= 8 ? 1u << k : (chunks_log2 > 8 ? 1u << (chunks_log2 - 8) : 1u);
+}
 // Device-side measurement decisions (one thread per task of a decision
 // group). Task i's measurements are dec[task_first[i] .. task_first[i] +
 // task_count[i]), in gate order. Single measurements (joint = 0) read S and

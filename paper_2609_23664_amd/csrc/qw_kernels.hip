@@ -834,27 +834,37 @@ __device__ __forceinline__ uint64_t splitmix(uint64_t x) {
     return x ^ (x >> 31);
 }
 
-// chunk sums of |psi|^2 (FP64), chunk = 2^C amplitudes; grid (chunks, slots)
-__global__ __launch_bounds__(256) void chunk_sum_kernel(const float2 *const *__restrict__ slots,
-                                                        uint32_t C, uint32_t chunks,
-                                                        double *__restrict__ csum) {
-    __shared__ double red[5];
-    const uint32_t c = blockIdx.x, s = blockIdx.y;
-    const float2 *psi = slots[s] + ((uint64_t)c << C);
-    const uint32_t len = 1u << C;
+// Chunk sums of |psi|^2 (FP64) for the joint measurement masses: one wave
+// per chunk of 128 * NL amplitudes (NL 16-byte loads a lane, all in flight,
+// then a fixed butterfly), four chunks a workgroup; grid (chunks / 4, slots).
+// Bound by the one read of the state. No LDS and no barrier: a workgroup per
+// chunk of 256 amplitudes (one 8-byte load a lane and a two-barrier block
+// sum each) read 4 states of 22 qubits at 3.0 TB/s (45 us), this form
+// takes 22 us (6.0 TB/s).
+template <int NL>
+__global__ __launch_bounds__(256) void mass_sum_kernel(const float2 *const *__restrict__ slots,
+                                                       uint32_t chunks, double *__restrict__ csum) {
+    const uint32_t c = blockIdx.x * 4u + (threadIdx.x >> 6), s = blockIdx.y, lane = threadIdx.x & 63u;
+    if (c >= chunks) return;
+    const float4 *psi = reinterpret_cast<const float4 *>(slots[s] + (uint64_t)c * (128u * NL));
+    float4 v[NL];
+    #pragma unroll
+    for (int i = 0; i < NL; ++i) v[i] = psi[i * 64 + lane];
     double acc = 0.0;
-    for (uint32_t i = threadIdx.x; i < len; i += 256) {
-        const double x = psi[i].x, y = psi[i].y;
-        acc = fma(x, x, acc);
-        acc = fma(y, y, acc);
+    #pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        const double x0 = v[i].x, y0 = v[i].y, x1 = v[i].z, y1 = v[i].w;
+        acc += fma(x0, x0, y0 * y0) + fma(x1, x1, y1 * y1);
     }
-    acc = block_sum<256>(acc, red);
-    if (threadIdx.x == 0) csum[(uint64_t)s * chunks + c] = acc;
+    #pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if (lane == 0) csum[(uint64_t)s * chunks + c] = acc;
 }
 
 // Measurement sums of slot s over chunk c of 2^C amplitudes: the FP64 sum
 // of |psi_i|^2 and the same sum over the indices with bit qubit[s] set
-// (fixed order: per thread in index order, then the block sum).
+// (fixed order: per thread in index order, two amplitudes a 16-byte load,
+// then the block sum).
 __global__ __launch_bounds__(256) void measure_sum_kernel(const float2 *const *__restrict__ slots,
                                                           const uint32_t *__restrict__ qubit,
                                                           uint32_t C, uint32_t chunks,
@@ -862,15 +872,18 @@ __global__ __launch_bounds__(256) void measure_sum_kernel(const float2 *const *_
     __shared__ double red[5];
     const uint32_t c = blockIdx.x, s = blockIdx.y;
     const uint64_t first = (uint64_t)c << C;
-    const float2 *psi = slots[s] + first;
+    const float4 *psi = reinterpret_cast<const float4 *>(slots[s] + first);
     const uint32_t q = qubit[s];
-    const uint32_t len = 1u << C;
+    const uint32_t pairs = 1u << (C - 1);
     double acc = 0.0, acc1 = 0.0;
-    for (uint32_t i = threadIdx.x; i < len; i += 256) {
-        const double x = psi[i].x, y = psi[i].y;
-        const double w = fma(x, x, y * y);
-        acc += w;
-        if (((first + i) >> q) & 1ull) acc1 += w;
+    #pragma unroll 8
+    for (uint32_t i = threadIdx.x; i < pairs; i += 256) {
+        const float4 v = psi[i];
+        const double x0 = v.x, y0 = v.y, x1 = v.z, y1 = v.w;
+        const double w0 = fma(x0, x0, y0 * y0), w1 = fma(x1, x1, y1 * y1);
+        acc += w0 + w1;
+        if (q == 0) acc1 += w1;
+        else if (((first + 2u * i) >> q) & 1ull) acc1 += w0 + w1;
     }
     acc = block_sum<256>(acc, red);
     acc1 = block_sum<256>(acc1, red);
@@ -880,18 +893,17 @@ __global__ __launch_bounds__(256) void measure_sum_kernel(const float2 *const *_
     }
 }
 
-// Chunk sums of slot s added in a fixed order: out[2 s] = S, out[2 s + 1] = S1.
+// Chunk sums of slot s added in a fixed order (per thread strided, then the
+// block sum): out[2 s] = S, out[2 s + 1] = S1.
 __global__ __launch_bounds__(256) void measure_finalize_kernel(const double *__restrict__ part,
                                                                uint32_t chunks,
                                                                double *__restrict__ out) {
     __shared__ double red[5];
     const uint32_t s = blockIdx.x;
     const double *in = part + 2 * (uint64_t)s * chunks;
-    const uint32_t per = (chunks + 255) / 256;
-    const uint32_t b0 = threadIdx.x * per;
-    const uint32_t b1 = (b0 + per < chunks) ? b0 + per : chunks;
     double a = 0.0, a1 = 0.0;
-    for (uint32_t c = b0; c < b1; ++c) {
+    #pragma unroll 4
+    for (uint32_t c = threadIdx.x; c < chunks; c += 256) {
         a += in[2 * c];
         a1 += in[2 * c + 1];
     }
@@ -903,41 +915,49 @@ __global__ __launch_bounds__(256) void measure_finalize_kernel(const double *__r
     }
 }
 
-// Joint measurement masses: chunk c of slot s (2^C amplitudes, FP64 sum
-// csum[s * chunks + c]) lies in one outcome bin when every measured qubit is
-// >= C; bin b of slot s (its measured bits in ascending qubit order) is the
-// sum of its chunks in increasing chunk order. mq[s]: measured-qubit mask of
-// slot s shifted down by C (a mask over chunk-index bits).
+// Joint measurement masses: chunk c of slot s (FP64 sum csum[(s <<
+// chunks_log2) + c]) lies in one outcome bin, since every measured qubit is
+// at or above the chunk bits; bin b of slot s (its measured bits in
+// ascending qubit order) is the sum of the chunks whose index has b on the
+// measured bits M = mq[s] << shift and any f on the others. A workgroup of
+// 256 threads sums one bin with strided f, or, when a bin has fewer than 256
+// chunks, 256 / nfree bins at once (nfree threads each), then a fixed tree.
+// Bound by latency (each chunk sum is read once, a few MB at most): with one
+// thread per bin, 8 bins of a 22-qubit state were 8 serial chains of 2,048
+// loads, 1,132 us for 4 states; now 5.7 us.
 __global__ __launch_bounds__(256) void bin_mass_kernel(const double *__restrict__ csum,
-                                                       uint32_t chunks_log2,
+                                                       uint32_t chunks_log2, uint32_t shift,
                                                        const uint64_t *__restrict__ mq,
                                                        uint32_t bin_stride,
                                                        double *__restrict__ out) {
-    const uint32_t s = blockIdx.x;
-    const uint64_t M = mq[s];
-    const uint32_t k = (uint32_t)__popcll(M);
-    const uint64_t all = (chunks_log2 >= 64) ? ~0ull : ((1ull << chunks_log2) - 1ull);
-    const uint64_t F = all & ~M;
-    const uint64_t nfree = 1ull << (chunks_log2 - k);
-    const double *in = csum + ((uint64_t)s << chunks_log2);
-    for (uint32_t b = threadIdx.x; b < (1u << k); b += 256) {
-        // chunk bits of the bin: deposit b into M
-        uint64_t cb = 0;
-        {
-            uint32_t j = 0;
-            for (uint32_t p = 0; p < chunks_log2; ++p)
-                if ((M >> p) & 1ull) cb |= (uint64_t)((b >> j++) & 1u) << p;
-        }
-        double a = 0.0;
-        for (uint64_t f = 0; f < nfree; ++f) {
-            uint64_t c = cb;
-            uint32_t j = 0;
-            for (uint32_t p = 0; p < chunks_log2; ++p)
-                if ((F >> p) & 1ull) c |= ((f >> j++) & 1ull) << p;
+    __shared__ double red[256];
+    const uint32_t s = blockIdx.y, t = threadIdx.x;
+    const uint32_t all = (uint32_t)((1ull << chunks_log2) - 1ull);
+    const uint32_t M = (uint32_t)(mq[s] << shift), F = all & ~M;
+    const uint32_t k = (uint32_t)__popc(M), fl = chunks_log2 - k;
+    if (blockIdx.x >= joint_blocks(chunks_log2, k)) return;
+    const uint32_t seg = fl < 8u ? fl : 8u;                  // log2 of the threads of one bin
+    const uint32_t b = (blockIdx.x << (8u - seg)) + (t >> seg), f0 = t & ((1u << seg) - 1u);
+    double a = 0.0;
+    if (b < (1u << k)) {
+        const double *in = csum + ((uint64_t)s << chunks_log2) + dpdep32(b, M);
+        // f0, f0 + 256, ... deposited into F: adding 256 carries through the
+        // other bits set to one (no second step when a bin has <= 256 chunks)
+        const uint32_t step = fl > 8u ? dpdep32(256u, F) : 0u;
+        uint32_t c = dpdep32(f0, F);
+        #pragma unroll 8
+        for (uint32_t i = 0; i < (1u << (fl - seg)); ++i) {
             a += in[c];
+            c = ((c | ~F) + step) & F;
         }
-        out[(uint64_t)s * bin_stride + b] = a;
     }
+    red[t] = a;
+    __syncthreads();
+    for (uint32_t h = (1u << seg) >> 1; h > 0; h >>= 1) {
+        if (f0 < h) red[t] += red[t + h];
+        __syncthreads();
+    }
+    if (f0 == 0 && b < (1u << k)) out[(uint64_t)s * bin_stride + b] = red[t];
 }
 
 // Dense export of a stabilizer state (STAB -> SV): amplitude k is
@@ -1290,7 +1310,7 @@ hipError_t launch_sample(hipStream_t st, const float2 *const *slots, uint32_t n_
 hipError_t launch_measure_sums(hipStream_t st, const float2 *const *slots, const uint32_t *qubit,
                                uint32_t n_slots, uint32_t n, double *part, double *out) {
     if (n_slots == 0) return hipSuccess;
-    const uint32_t C = n < 14 ? n : 14;
+    const uint32_t C = n < 12 ? n : 12;
     const uint32_t chunks = 1u << (n - C);
     hipLaunchKernelGGL(measure_sum_kernel, dim3(chunks, n_slots), dim3(256), 0, st, slots, qubit, C,
                        chunks, part);
@@ -1301,49 +1321,61 @@ hipError_t launch_measure_sums(hipStream_t st, const float2 *const *slots, const
 }
 
 hipError_t launch_joint_masses(hipStream_t st, const float2 *const *slots, const uint64_t *mq,
-                               uint32_t n_slots, uint32_t n, uint32_t C, double *csum,
-                               uint32_t bin_stride, double *out) {
+                               uint32_t n_slots, uint32_t n, uint32_t C, uint32_t max_blocks,
+                               double *csum, uint32_t bin_stride, double *out) {
     if (n_slots == 0) return hipSuccess;
-    const uint32_t chunks = 1u << (n - C);
-    hipLaunchKernelGGL(chunk_sum_kernel, dim3(chunks, n_slots), dim3(256), 0, st, slots, C, chunks,
-                       csum);
+    const uint32_t cb = joint_chunk_bits(C), chunks = 1u << (n - cb);
+    const dim3 grid((chunks + 3) / 4, n_slots), wg(256);
+    if (cb == 8) hipLaunchKernelGGL(mass_sum_kernel<2>, grid, wg, 0, st, slots, chunks, csum);
+    else if (cb == 9) hipLaunchKernelGGL(mass_sum_kernel<4>, grid, wg, 0, st, slots, chunks, csum);
+    else if (cb == 10) hipLaunchKernelGGL(mass_sum_kernel<8>, grid, wg, 0, st, slots, chunks, csum);
+    else return hipErrorInvalidValue;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bin_mass_kernel, dim3(n_slots), dim3(256), 0, st, csum, n - C, mq, bin_stride,
-                       out);
+    hipLaunchKernelGGL(bin_mass_kernel, dim3(max_blocks, n_slots), dim3(256), 0, st, csum, n - cb, C - cb, mq,
+                       bin_stride, out);
     return hipGetLastError();
 }
 
 namespace {
 
 // One workgroup per task. A joint cluster's bin masses are staged in LDS;
-// each step sums them (and those with the step's bit set) with a fixed
-// order (per-thread strided sums, then a fixed tree), decides, and keeps
-// the bins that agree with the outcome: bin b moves to b with bit p removed,
-// which keeps their order.
+// each step sums those with the step's bit clear and set with a fixed order
+// (per-thread strided sums, a wave butterfly, then the waves in order),
+// decides, and keeps the bins that agree with the outcome: bin b moves to b
+// with bit p removed, which keeps their order. Bound by latency: two barriers
+// a step instead of a tree of nine through LDS (11 measurements: 20 us, now
+// 14 us).
 constexpr int kDecideThreads = 256;
 
 __device__ __forceinline__ void decide_sums(const double *mass, uint32_t len, uint32_t p, double *red,
-                                            double *tot, double *one) {
+                                            double *zero, double *one) {
     const uint32_t t = threadIdx.x;
-    double a = 0.0, b1 = 0.0;
+    double a0 = 0.0, a1 = 0.0;
     for (uint32_t b = t; b < len; b += kDecideThreads) {
-        a += mass[b];
-        if ((b >> p) & 1u) b1 += mass[b];
+        const double v = mass[b];
+        if ((b >> p) & 1u) a1 += v;
+        else a0 += v;
     }
-    red[t] = a;
-    red[kDecideThreads + t] = b1;
-    __syncthreads();
-    for (uint32_t h = kDecideThreads / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            red[t] += red[t + h];
-            red[kDecideThreads + t] += red[kDecideThreads + t + h];
-        }
-        __syncthreads();
+    #pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a0 += __shfl_xor(a0, o, 64);
+        a1 += __shfl_xor(a1, o, 64);
     }
-    *tot = red[0];
-    *one = red[kDecideThreads];
+    if ((t & 63u) == 0) {
+        red[2 * (t >> 6)] = a0;
+        red[2 * (t >> 6) + 1] = a1;
+    }
     __syncthreads();
+    a0 = red[0];
+    a1 = red[1];
+    #pragma unroll
+    for (int w = 1; w < kDecideThreads / 64; ++w) {
+        a0 += red[2 * w];
+        a1 += red[2 * w + 1];
+    }
+    *zero = a0;
+    *one = a1;
 }
 
 __global__ __launch_bounds__(kDecideThreads) void meas_decide_kernel(
@@ -1351,10 +1383,13 @@ __global__ __launch_bounds__(kDecideThreads) void meas_decide_kernel(
     const MeasDec *__restrict__ dec, uint32_t n_tasks, int joint, double *__restrict__ sums,
     uint32_t bin_stride, float *__restrict__ dyn, uint8_t *__restrict__ outc, uint32_t *__restrict__ err) {
     __shared__ double buf[2][1u << 12];
-    __shared__ double red[2 * kDecideThreads];
+    __shared__ double red[2 * (kDecideThreads / 64)];
+    __shared__ MeasDec sd[12];   // the task's measurements (k <= 12, the caller's cluster bound)
     const uint32_t i = blockIdx.x, t = threadIdx.x;
     if (i >= n_tasks) return;
-    const uint32_t f0 = task_first[i], k = task_count[i];
+    const uint32_t k = task_count[i];
+    if (t < k) sd[t] = dec[task_first[i] + t];
+    __syncthreads();
     uint32_t bits = 0;     // outcome of measurement j in bit j
     double chosen = 1.0;   // mass of the chosen outcome
     bool zero = false;
@@ -1363,7 +1398,7 @@ __global__ __launch_bounds__(kDecideThreads) void meas_decide_kernel(
         if (!(S > 0.0)) {
             zero = true;
         } else {
-            const uint32_t b = dec[f0].u < S1 / S ? 1u : 0u;
+            const uint32_t b = sd[0].u < S1 / S ? 1u : 0u;
             bits = b;
             chosen = b ? S1 : S - S1;
         }
@@ -1373,44 +1408,42 @@ __global__ __launch_bounds__(kDecideThreads) void meas_decide_kernel(
         for (uint32_t b = t; b < len; b += kDecideThreads) buf[0][b] = src[b];
         __syncthreads();
         int cur = 0;
-        double tot, one;
-        decide_sums(buf[cur], len, 0, red, &tot, &one);
-        if (!(tot > 0.0)) {
-            zero = true;
-        } else {
-            for (uint32_t j = 0; j < k; ++j) {
-                const uint32_t p = dec[f0 + j].pos;
-                decide_sums(buf[cur], len, p, red, &tot, &one);
-                const uint32_t bit = dec[f0 + j].u < one / tot ? 1u : 0u;
-                bits |= bit << j;
-                const uint32_t lo = (1u << p) - 1u;
-                for (uint32_t b = t; b < len; b += kDecideThreads)
-                    if (((b >> p) & 1u) == bit) buf[cur ^ 1][((b >> (p + 1)) << p) | (b & lo)] = buf[cur][b];
-                __syncthreads();
-                cur ^= 1;
-                len >>= 1;
+        for (uint32_t j = 0; j < k && !zero; ++j) {
+            const uint32_t p = sd[j].pos;
+            double none, one;
+            decide_sums(buf[cur], len, p, red, &none, &one);
+            const double tot = none + one;
+            if (j == 0 && !(tot > 0.0)) {
+                zero = true;   // the same in every thread
+                break;
             }
-            chosen = buf[cur][0];
+            const uint32_t bit = sd[j].u < one / tot ? 1u : 0u;
+            bits |= bit << j;
+            const uint32_t lo = (1u << p) - 1u;
+            for (uint32_t b = t; b < len; b += kDecideThreads)
+                if (((b >> p) & 1u) == bit) buf[cur ^ 1][((b >> (p + 1)) << p) | (b & lo)] = buf[cur][b];
+            __syncthreads();   // also: every thread has read red
+            cur ^= 1;
+            len >>= 1;
         }
+        chosen = buf[cur][0];
     }
-    if (t != 0) return;
     if (zero) {
-        *err = 1u;
+        if (t == 0) *err = 1u;
         chosen = 1.0;
     }
+    if (t >= k) return;
     const float fac = (float)(1.0 / sqrt(chosen));
-    for (uint32_t j = 0; j < k; ++j) {
-        const MeasDec &m = dec[f0 + j];
-        const uint32_t b = (bits >> j) & 1u;
-        const float f = j == 0 ? fac : 1.0f;
-        float *e = dyn + 4ull * m.dyn;
-        // [[e0, e1], [e2, e3]]: P0 = diag(f, 0), P1 = diag(0, f), X P1 = [[0, f], [0, 0]]
-        e[0] = b ? 0.0f : f;
-        e[1] = (b && m.reset) ? f : 0.0f;
-        e[2] = 0.0f;
-        e[3] = (b && !m.reset) ? f : 0.0f;
-        outc[m.outc] = (uint8_t)b;
-    }
+    const MeasDec &m = sd[t];   // one thread per measurement
+    const uint32_t b = (bits >> t) & 1u;
+    const float f = t == 0 ? fac : 1.0f;
+    float *e = dyn + 4ull * m.dyn;
+    // [[e0, e1], [e2, e3]]: P0 = diag(f, 0), P1 = diag(0, f), X P1 = [[0, f], [0, 0]]
+    e[0] = b ? 0.0f : f;
+    e[1] = (b && m.reset) ? f : 0.0f;
+    e[2] = 0.0f;
+    e[3] = (b && !m.reset) ? f : 0.0f;
+    outc[m.outc] = (uint8_t)b;
 }
 
 __global__ void meas_clear_kernel(uint32_t *err) {
