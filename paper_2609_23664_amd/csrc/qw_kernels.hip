@@ -1074,101 +1074,180 @@ __global__ __launch_bounds__(256) void stab_export_kernel(float2 *__restrict__ p
     }
 }
 
-// exclusive prefix of chunk sums per slot (in place into cpre) + total
-__global__ __launch_bounds__(256) void chunk_scan_kernel(const double *__restrict__ csum,
-                                                         uint32_t chunks,
-                                                         double *__restrict__ cpre,
-                                                         double *__restrict__ total) {
-    __shared__ double seg[256];
-    const uint32_t s = blockIdx.x;
+// Exclusive prefix of a slot's chunk sums and its total, in FP64 with a
+// fixed order: blocks of 1,024 threads * PER consecutive chunks, per thread in
+// order, thread sums by a wave scan, wave sums in order, blocks in order. One
+// workgroup per slot; PER = 16 takes its chunks through LDS (rows of 16 padded
+// to 17) so that global accesses stay coalesced, PER = 1 serves states of at
+// most 1,024 chunks (20 qubits). Bound by latency and one CU's access rate:
+// 256 threads that walked 64 chunks each twice, with a serial scan of the 256
+// sums between, took 32 us for one 24-qubit state (16,384 chunks); 16
+// consecutive loads a thread straight from memory 18 us; this 8.0 us.
+template <int PER>
+__global__ __launch_bounds__(1024) void chunk_scan_kernel(const double *__restrict__ csum,
+                                                          uint32_t chunks,
+                                                          double *__restrict__ cpre,
+                                                          double *__restrict__ total) {
+    __shared__ double wsum[16];
+    __shared__ double stage[PER > 1 ? 1024 * (PER + 1) : 1];
+    const uint32_t s = blockIdx.x, t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const double *in = csum + (uint64_t)s * chunks;
     double *outp = cpre + (uint64_t)s * chunks;
-    const uint32_t per = (chunks + 255) / 256;
-    const uint32_t b0 = threadIdx.x * per;
-    const uint32_t b1 = (b0 + per < chunks) ? b0 + per : chunks;
-    double acc = 0.0;
-    for (uint32_t c = b0; c < b1; ++c) acc += in[c];
-    seg[threadIdx.x] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double run = 0.0;
-        for (int k = 0; k < 256; ++k) {
-            const double t = seg[k];
-            seg[k] = run;
-            run += t;
+    auto at = [](uint32_t c) { return c + c / PER; };
+    double carry = 0.0;
+    for (uint32_t b0 = 0; b0 < chunks; b0 += 1024u * PER) {
+        double v[PER], acc = 0.0;
+        #pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            const uint32_t c = i * 1024u + t;
+            v[i] = b0 + c < chunks ? in[b0 + c] : 0.0;
         }
-        total[s] = run;
+        if constexpr (PER > 1) {
+            #pragma unroll
+            for (uint32_t i = 0; i < PER; ++i) stage[at(i * 1024u + t)] = v[i];
+            __syncthreads();
+            #pragma unroll
+            for (uint32_t i = 0; i < PER; ++i) v[i] = stage[at(t * PER + i)];
+        }
+        #pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) acc += v[i];
+        double x = acc;   // inclusive wave scan of the thread sums
+        #pragma unroll
+        for (uint32_t o = 1; o < 64u; o <<= 1) {
+            const double y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63u) wsum[wave] = x;
+        __syncthreads();
+        double off = carry, all = carry;
+        #pragma unroll
+        for (uint32_t w = 0; w < 16u; ++w) {
+            if (w < wave) off += wsum[w];
+            all += wsum[w];
+        }
+        const double before = __shfl_up(x, 1, 64);
+        double run = lane ? off + before : off;
+        #pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            const double r = run;
+            run += v[i];
+            v[i] = r;
+        }
+        if constexpr (PER > 1) {
+            #pragma unroll
+            for (uint32_t i = 0; i < PER; ++i) stage[at(t * PER + i)] = v[i];   // the thread's own entries
+            __syncthreads();
+            #pragma unroll
+            for (uint32_t i = 0; i < PER; ++i) v[i] = stage[at(i * 1024u + t)];
+        }
+        #pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            const uint32_t c = b0 + i * 1024u + t;
+            if (c < chunks) outp[c] = v[i];
+        }
+        carry = all;
+        __syncthreads();
+    }
+    if (t == 0) total[s] = carry;
+}
+
+// Sub-chunk (64 amplitudes) and chunk (1,024) sums of |psi|^2 (FP64) for the
+// sampler, one wave per chunk; grid (chunks / 4, slots). A lane takes two
+// amplitudes of each of 8 sub-chunks (8 loads of 16 bytes, all in flight); a
+// sub-chunk's 32 lane values are added by the butterfly 16, 8, 4, 2, 1, the
+// number of sub-chunks per lane halving in its first three steps; the chunk
+// sum is the sequential sum of its sub-chunk sums. Bound by the one read of
+// the state: a workgroup per chunk with one load a lane at a time read a
+// 24-qubit state at 4.7 TB/s (28.5 us), this takes 20.5 us (6.5 TB/s).
+__global__ __launch_bounds__(256) void sub_sum_kernel(const float2 *const *__restrict__ slots,
+                                                      uint32_t chunks, double *__restrict__ csum,
+                                                      double *__restrict__ ssum) {
+    __shared__ double subs[4][16];
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    const uint32_t c = blockIdx.x * 4u + wave, s = blockIdx.y;
+    const bool ok = c < chunks;
+    if (ok) {
+        const float4 *psi = reinterpret_cast<const float4 *>(slots[s] + ((uint64_t)c << 10));
+        float4 a[8];
+        #pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = psi[i * 64 + lane];
+        double v[8];   // sub-chunk 2 i + (lane >> 5)
+        #pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const double x0 = a[i].x, y0 = a[i].y, x1 = a[i].z, y1 = a[i].w;
+            v[i] = fma(x0, x0, y0 * y0) + fma(x1, x1, y1 * y1);
+        }
+        const bool b4 = lane & 16u, b3 = lane & 8u, b2 = lane & 4u;
+        double f[4], g[2], h;
+        #pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = (b4 ? v[4 + i] : v[i]) + __shfl_xor(b4 ? v[i] : v[4 + i], 16, 64);
+        #pragma unroll
+        for (int i = 0; i < 2; ++i) g[i] = (b3 ? f[2 + i] : f[i]) + __shfl_xor(b3 ? f[i] : f[2 + i], 8, 64);
+        h = (b2 ? g[1] : g[0]) + __shfl_xor(b2 ? g[0] : g[1], 4, 64);
+        h += __shfl_xor(h, 2, 64);
+        h += __shfl_xor(h, 1, 64);
+        // lane bits 4, 3, 2 hold the load index, bit 5 the half
+        if ((lane & 3u) == 0u) {
+            const uint32_t i = 4u * ((lane >> 4) & 1u) + 2u * ((lane >> 3) & 1u) + ((lane >> 2) & 1u);
+            const uint32_t j = 2u * i + (lane >> 5);
+            subs[wave][j] = h;
+            ssum[((uint64_t)s * chunks + c) * 16u + j] = h;
+        }
     }
     __syncthreads();
-    double run = seg[threadIdx.x];
-    for (uint32_t c = b0; c < b1; ++c) {
-        outp[c] = run;
-        run += in[c];
+    if (ok && lane == 0) {
+        double acc = 0.0;
+        #pragma unroll
+        for (int j = 0; j < 16; ++j) acc += subs[wave][j];
+        csum[(uint64_t)s * chunks + c] = acc;
     }
 }
 
-// Sub-chunk and chunk sums of |psi|^2 (FP64) for the sampler; grid (chunks,
-// slots), chunk = 2^C amplitudes, sub-chunk = 2^S (S <= 6) amplitudes. A
-// sub-chunk of 64 is summed by 32 lanes (two amplitudes each, then a fixed
-// butterfly), a smaller one by one amplitude per lane; the chunk sum is the
-// sequential sum of its sub-chunk sums.
-__global__ __launch_bounds__(256) void sub_sum_kernel(const float2 *const *__restrict__ slots,
-                                                      uint32_t C, uint32_t S, uint32_t chunks,
-                                                      double *__restrict__ csum,
-                                                      double *__restrict__ ssum) {
-    __shared__ double subs[16];
-    const uint32_t c = blockIdx.x, s = blockIdx.y;
-    const uint32_t spc = 1u << (C - S), L = 1u << S;
-    const float2 *psi = slots[s] + ((uint64_t)c << C);
+// The same for states below 10 qubits: one chunk of 2^n amplitudes, its
+// sub-chunks of 2^S (S <= 6) summed by one amplitude per lane.
+__global__ __launch_bounds__(256) void sub_sum_small_kernel(const float2 *const *__restrict__ slots,
+                                                            uint32_t n, uint32_t S,
+                                                            double *__restrict__ csum,
+                                                            double *__restrict__ ssum) {
+    __shared__ double subs[8];
+    const uint32_t s = blockIdx.x, spc = 1u << (n - S), L = 1u << S;
+    const float2 *psi = slots[s];
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    double *out = ssum + ((uint64_t)s * chunks + c) * spc;
-    if (S == 6) {
-        // two sub-chunks per wave step: each half-wave covers one with two
-        // amplitudes (16 bytes) per lane
-        const uint32_t half = lane >> 5, hl = lane & 31;
-        for (uint32_t q = wave; 2 * q < spc; q += 4) {
-            const uint32_t j = 2 * q + half;
-            double v = 0.0;
-            if (j < spc) {
-                const float4 a = *reinterpret_cast<const float4 *>(psi + (j << 6) + 2 * hl);
-                const double x0 = a.x, y0 = a.y, x1 = a.z, y1 = a.w;
-                v = fma(x0, x0, y0 * y0) + fma(x1, x1, y1 * y1);
-            }
-            for (int o = 16; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (hl == 0 && j < spc) {
-                subs[j] = v;
-                out[j] = v;
-            }
+    for (uint32_t j = wave; j < spc; j += 4) {
+        double v = 0.0;
+        if (lane < L) {
+            const float2 a = psi[(j << S) + lane];
+            const double x = a.x, y = a.y;
+            v = fma(x, x, y * y);
         }
-    } else {
-        for (uint32_t j = wave; j < spc; j += 4) {
-            double v = 0.0;
-            if (lane < L) {
-                const float2 a = psi[(j << S) + lane];
-                const double x = a.x, y = a.y;
-                v = fma(x, x, y * y);
-            }
-            for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) {
-                subs[j] = v;
-                out[j] = v;
-            }
+        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (lane == 0) {
+            subs[j] = v;
+            ssum[(uint64_t)s * spc + j] = v;
         }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         double acc = 0.0;
         for (uint32_t j = 0; j < spc; ++j) acc += subs[j];
-        csum[(uint64_t)s * chunks + c] = acc;
+        csum[s] = acc;
     }
 }
 
-// One thread per (slot, shot). The target u * total is located by a binary
-// search over the chunk prefixes, a scan of the chunk's sub-chunk sums and a
-// scan of one sub-chunk's amplitudes, the running sum continuing in FP64 from
-// the chunk prefix. Where rounding leaves the target past a level's last
-// element, that level's last element of non-zero mass is taken, so every
-// outcome has non-zero probability.
+// 8 lanes per (slot, shot), 32 shots per workgroup. The target u * total is
+// located by an 8-way search over the chunk prefixes, a scan of the chunk's
+// (at most 16) sub-chunk sums and a scan of one sub-chunk's (at most 64)
+// amplitudes, the running sum continuing in FP64 from the chunk prefix, one
+// element after the other. Where rounding leaves the target past a level's
+// last element, that level's last element of non-zero mass is taken, so every
+// outcome has non-zero probability. Few shots are bound by the chain of
+// dependent loads, which 8 lanes shorten (one thread per shot waited for
+// log2(chunks) + up to 80 of them); many by the scans, so the amplitudes of
+// the 32 shots go through LDS and one lane per shot adds them. 1,024 shots of
+// a 24-qubit state: 21 us with one thread per shot, now 8.4 us; 65,536 shots
+// of 64 18-qubit states: 18 us, now 17 us.
+constexpr uint32_t kDrawLanes = 8, kDrawShots = 256 / kDrawLanes;
+
 __global__ __launch_bounds__(256) void draw_kernel(const float2 *const *__restrict__ slots,
                                                    uint32_t n_slots, uint32_t C, uint32_t S,
                                                    uint32_t chunks, const double *__restrict__ csum,
@@ -1177,56 +1256,106 @@ __global__ __launch_bounds__(256) void draw_kernel(const float2 *const *__restri
                                                    const double *__restrict__ total,
                                                    uint64_t seed, uint64_t task_base,
                                                    uint32_t shots, uint32_t *__restrict__ out) {
-    const uint64_t gid = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (gid >= (uint64_t)n_slots * shots) return;
-    const uint32_t s = (uint32_t)(gid / shots), sh = (uint32_t)(gid % shots);
-    const uint64_t h = splitmix(seed ^ (((task_base + s) << 32) + sh));
-    const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
-    const double target = u * total[s];
-    const double *pre = cpre + (uint64_t)s * chunks;
-    const double *cs = csum + (uint64_t)s * chunks;
-    // last chunk with pre[c] <= target, then back over chunks without mass
-    uint32_t lo = 0, hi = chunks - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (pre[mid] <= target) lo = mid;
-        else hi = mid - 1;
-    }
-    while (lo > 0 && cs[lo] == 0.0) --lo;
+    __shared__ double sub[kDrawShots][17];
+    __shared__ double prob[kDrawShots][65];   // (odd row lengths: the shots' columns lie in other banks)
+    __shared__ double s_at[kDrawShots], s_target[kDrawShots];
+    __shared__ uint32_t s_base[kDrawShots];
+    const uint32_t lane = threadIdx.x & (kDrawLanes - 1), shot = threadIdx.x / kDrawLanes;
+    const uint32_t group = (threadIdx.x & 63u) & ~(kDrawLanes - 1);
     const uint32_t spc = 1u << (C - S), L = 1u << S;
-    const double *sb = ssum + ((uint64_t)s * chunks + lo) * spc;
-    double run = pre[lo], run_last = run;
-    int j = -1, last_j = 0;
-    for (uint32_t k = 0; k < spc; ++k) {
-        const double v = sb[k];
-        if (v > 0.0) {
-            last_j = (int)k;
-            run_last = run;
+    const uint64_t all = (uint64_t)n_slots * shots;
+    for (uint64_t first = (uint64_t)blockIdx.x * kDrawShots; first < all; first += (uint64_t)gridDim.x * kDrawShots) {
+        const uint64_t want = first + shot;
+        const uint64_t gid = want < all ? want : all - 1;   // idle groups repeat the last shot
+        uint32_t s, sh;
+        if (all <= 0xFFFFFFFFull) {   // a 32-bit division where it suffices
+            s = (uint32_t)gid / shots;
+            sh = (uint32_t)gid - s * shots;
+        } else {
+            s = (uint32_t)(gid / shots);
+            sh = (uint32_t)(gid % shots);
         }
-        if (run + v > target) {
-            j = (int)k;
-            break;
+        const uint64_t h = splitmix(seed ^ (((task_base + s) << 32) + sh));
+        const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
+        const double target = u * total[s];
+        const double *pre = cpre + (uint64_t)s * chunks;
+        const double *cs = csum + (uint64_t)s * chunks;
+        // last chunk with pre[c] <= target, then back over chunks without mass
+        uint32_t lo = 0, len = chunks;
+        while (len > 1u) {
+            const uint32_t stride = len >= kDrawLanes ? len / kDrawLanes : 1u;
+            const bool in = lane * stride < len && pre[lo + lane * stride] <= target;
+            const uint32_t hit = (uint32_t)(__ballot(in) >> group) & ((1u << kDrawLanes) - 1u);
+            lo += hit ? (31u - (uint32_t)__clz(hit)) * stride : 0u;
+            len = stride;
         }
-        run += v;
-    }
-    if (j < 0) {
-        j = last_j;
-        run = run_last;
-    }
-    const float2 *psi = slots[s] + ((uint64_t)lo << C) + ((uint64_t)j << S);
-    uint32_t res = 0xFFFFFFFFu, last_i = 0;
-    for (uint32_t i = 0; i < L; ++i) {
-        const double x = psi[i].x, y = psi[i].y;
-        const double pr = fma(x, x, y * y);
-        if (pr > 0.0) last_i = i;
-        run += pr;
-        if (run > target) {
-            res = i;
-            break;
+        while (lo > 0 && cs[lo] == 0.0) --lo;
+        const double *sb = ssum + ((uint64_t)s * chunks + lo) * spc;
+        double run = pre[lo], run_last = run;
+        #pragma unroll
+        for (uint32_t i = 0; i < 16 / kDrawLanes; ++i)
+            if (i * kDrawLanes + lane < spc) sub[shot][i * kDrawLanes + lane] = sb[i * kDrawLanes + lane];
+        lds_wave_sync();
+        // j: the first element that takes the running sum past the target
+        // (counted without branches), else the last one of non-zero mass
+        uint32_t j = 0, last_j = 0;
+        double at = run;   // running sum before element j
+        bool past = false;
+        #pragma unroll 4
+        for (uint32_t k = 0; k < spc; ++k) {
+            const double v = sub[shot][k];
+            at = past ? at : run;
+            last_j = v > 0.0 ? k : last_j;
+            run_last = v > 0.0 ? run : run_last;
+            run += v;
+            past = past || run > target;
+            j += past ? 0u : 1u;
         }
+        if (!past) {
+            j = last_j;
+            at = run_last;
+        }
+        const uint64_t base = ((uint64_t)lo << C) + ((uint64_t)j << S);
+        const float2 *psi = slots[s] + base;
+        #pragma unroll
+        for (uint32_t i = 0; i < 64 / kDrawLanes; ++i) {
+            const uint32_t l = i * kDrawLanes + lane;
+            if (l < L) {
+                const float2 a = psi[l];
+                const double x = a.x, y = a.y;
+                prob[shot][l] = fma(x, x, y * y);
+            }
+        }
+        if (lane == 0) {
+            s_at[shot] = at;
+            s_target[shot] = target;
+            s_base[shot] = (uint32_t)base;
+        }
+        __syncthreads();
+        const uint32_t q = threadIdx.x;
+        if (q < kDrawShots && first + q < all) {
+            const double tq = s_target[q];
+            double rq = s_at[q];
+            uint32_t res = 0, last_i = 0;
+            bool over = false;
+            auto step = [&](uint32_t i) {
+                const double pr = prob[q][i];
+                rq += pr;
+                last_i = pr > 0.0 ? i : last_i;
+                over = over || rq > tq;
+                res += over ? 0u : 1u;
+            };
+            if (L == 64u) {
+                #pragma unroll
+                for (uint32_t i = 0; i < 64u; ++i) step(i);
+            } else {
+                for (uint32_t i = 0; i < L; ++i) step(i);
+            }
+            if (!over) res = last_i;
+            out[first + q] = s_base[q] + res;
+        }
+        __syncthreads();   // the next shots reuse the LDS
     }
-    if (res == 0xFFFFFFFFu) res = last_i;
-    out[gid] = (uint32_t)(((uint64_t)lo << C) + ((uint64_t)j << S) + res);
 }
 
 // ------------------------------------------------------------- launchers
@@ -1361,19 +1490,24 @@ hipError_t launch_sample(hipStream_t st, const float2 *const *slots, uint32_t n_
                          uint64_t seed, uint64_t task_base, uint32_t shots, uint32_t *out) {
     const uint32_t C = sample_chunk_bits(n), S = sample_sub_bits(n);
     const uint32_t chunks = 1u << (n - C);
-    hipLaunchKernelGGL(sub_sum_kernel, dim3(chunks, n_slots), dim3(256), 0, st, slots, C, S, chunks,
-                       csum, ssum);
+    if (C == 10)
+        hipLaunchKernelGGL(sub_sum_kernel, dim3((chunks + 3) / 4, n_slots), dim3(256), 0, st, slots, chunks,
+                           csum, ssum);
+    else
+        hipLaunchKernelGGL(sub_sum_small_kernel, dim3(n_slots), dim3(256), 0, st, slots, C, S, csum, ssum);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(chunk_scan_kernel, dim3(n_slots), dim3(256), 0, st, csum, chunks, cpre,
-                       total);
+    if (chunks > 1024)
+        hipLaunchKernelGGL(chunk_scan_kernel<16>, dim3(n_slots), dim3(1024), 0, st, csum, chunks, cpre, total);
+    else
+        hipLaunchKernelGGL(chunk_scan_kernel<1>, dim3(n_slots), dim3(1024), 0, st, csum, chunks, cpre, total);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const uint64_t threads = (uint64_t)n_slots * shots;
-    if (threads == 0) return hipSuccess;
-    hipLaunchKernelGGL(draw_kernel, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, st,
-                       slots, n_slots, C, S, chunks, csum, cpre, ssum, total, seed, task_base, shots,
-                       out);
+    const uint64_t draws = (uint64_t)n_slots * shots;
+    if (draws == 0) return hipSuccess;
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>((draws + kDrawShots - 1) / kDrawShots, 1u << 20);
+    hipLaunchKernelGGL(draw_kernel, dim3(blocks), dim3(256), 0, st, slots, n_slots, C, S, chunks, csum, cpre,
+                       ssum, total, seed, task_base, shots, out);
     return hipGetLastError();
 }
 
