@@ -31,6 +31,34 @@ struct DevBuf {
     size_t cap = 0;
 };
 
+// Pinned host memory that kernels read or write.
+struct HostBuf {
+    void *p = nullptr;
+    size_t cap = 0;
+};
+
+// A staging slot: its memory, and the upload that reads it. Workgroup b of the
+// upload kernel sets the slot's word b to `seq` once it has read its part, so
+// the slot is free when its first `blocks` words hold `seq`.
+struct Stage {
+    HostBuf mem;
+    uint32_t seq = 0, blocks = 0;   // blocks = 0: nothing in flight
+};
+constexpr uint32_t kStageRing = 4;
+constexpr size_t kStageLarge = 1u << 20;
+
+// Staging of blobs of up to kStageTiny bytes: slots of one pinned block, in two
+// halves. An event behind a half's uploads is recorded when the other half is
+// entered and waited for before the half is used again.
+constexpr size_t kStageTiny = 16u << 10;
+constexpr uint32_t kTinyHalf = 16;
+struct TinyRing {
+    uint8_t *p = nullptr;
+    uint32_t next = 0;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    bool pending[2] = {false, false};
+};
+
 struct ProfRec {
     int kind;
     double bytes;
@@ -129,9 +157,14 @@ struct qw_ctx {
     uint64_t pingpong_cap = 16ull << 30;
     uint64_t mem_cap = 0;        // QW_OPT_DEVICE_MEM_CAP (0: none)
     uint64_t held = 0;           // bytes of the states and snapshot copies it allocated
-    void *staging = nullptr;
-    size_t staging_cap = 0;
-    hipEvent_t staging_ev = nullptr;
+    // pinned staging of plan uploads: tiny blobs; blobs of up to kStageLarge
+    // bytes, by kStageRing slots in turn; larger ones, by the last slot
+    TinyRing tiny;
+    Stage stage[kStageRing + 1];
+    uint32_t stage_next = 0;
+    uint32_t stage_seq = 0;             // number of the last upload
+    uint32_t *stage_done = nullptr;     // pinned: kUploadBlocks words per slot
+    HostBuf result;                     // pinned: host outputs the last kernel of a call writes
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
     KStats stats[4];
@@ -256,63 +289,80 @@ int ensure(qw_ctx *ctx, DevBuf &b, size_t bytes, const char *what) {
     return QW_OK;
 }
 
-// Copy a host blob to ctx->plan (device) through the pinned staging buffer.
-int upload(qw_ctx *ctx, const std::vector<uint8_t> &blob) {
-    if (blob.empty()) return QW_OK;
-    int rc = ensure(ctx, ctx->plan, blob.size(), "plan buffer");
-    if (rc) return rc;
-    if (ctx->rec) {
-        // recording: the blob is copied now, once, into a buffer the graph
-        // keeps (its nodes read it on every replay)
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->plan.p, blob.data(), blob.size(), hipMemcpyHostToDevice,
-                                    ctx->rec->up),
-                "plan upload (recording)");
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->rec->up), "plan upload (recording)");
-        ctx->rec->plan_used = true;
-        return QW_OK;
-    }
-    // the previous copy out of the staging buffer must have completed
-    HIP_TRY(ctx, hipEventSynchronize(ctx->staging_ev), "staging wait");
-    if (ctx->staging_cap < blob.size()) {
-        if (ctx->staging) HIP_TRY(ctx, hipHostFree(ctx->staging), "free staging");
-        ctx->staging = nullptr;
-        size_t want = std::max(blob.size(), ctx->staging_cap * 2);
-        HIP_TRY(ctx, hipHostMalloc(&ctx->staging, want, hipHostMallocDefault), "staging alloc");
-        ctx->staging_cap = want;
-    }
-    std::memcpy(ctx->staging, blob.data(), blob.size());
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->plan.p, ctx->staging, blob.size(), hipMemcpyHostToDevice,
-                                ctx->stream),
-            "plan upload");
-    HIP_TRY(ctx, hipEventRecord(ctx->staging_ev, ctx->stream), "staging event");
+// Pinned host memory of at least `bytes` (nothing may be using the old one).
+int ensure_host(qw_ctx *ctx, HostBuf &b, size_t bytes, const char *what) {
+    if (b.cap >= bytes) return QW_OK;
+    const size_t want = (std::max(bytes, b.cap * 2) + 4095) & ~size_t(4095);
+    if (b.p) HIP_TRY(ctx, hipHostFree(b.p), what);
+    b.p = nullptr;
+    b.cap = 0;
+    HIP_TRY(ctx, hipHostMalloc(&b.p, want, hipHostMallocDefault), what);
+    b.cap = want;
     return QW_OK;
 }
 
-// A blob built in place in the pinned staging buffer, which saves zeroing and
-// copying a host vector (a batch of 512 tasks of about 14 passes has a 25 MB
-// blob). stage_blob waits until the previous copy out of the buffer has
-// completed and grows it; upload_staged copies it to ctx->plan. Nothing else
-// may use the staging buffer in between. Padding between records is left as
-// it is: no kernel reads it.
+// Wait until the upload that reads a staging slot has read it. A failed
+// device ends the wait with its error (asked for every 4,096 polls).
+int stage_wait(qw_ctx *ctx, Stage &s, const uint32_t *done) {
+    for (uint32_t poll = 1; s.blocks; ++poll) {
+        uint32_t k = 0;
+        while (k < s.blocks && __atomic_load_n(done + k, __ATOMIC_ACQUIRE) == s.seq) ++k;
+        if (k == s.blocks) s.blocks = 0;
+        else if ((poll & 4095u) == 0u) {
+            const hipError_t e = hipStreamQuery(ctx->stream);
+            if (e == hipSuccess) s.blocks = 0;   // all enqueued work is done
+            else if (e != hipErrorNotReady) return hip_fail(ctx, e, "staging wait");
+        }
+    }
+    return QW_OK;
+}
+
+// A blob built in place in pinned staging memory and copied to ctx->plan.
+// stage_blob takes the next slot (waiting for its previous upload),
+// upload_staged enqueues the copy; nothing else may use the slot in between.
+// Padding between records is left as it is: no kernel reads it. Slots in turn
+// let the host prepare the next calls while the device works on earlier ones.
+// Up to 16 KiB the runtime's copy is the cheaper one, as long as no event
+// follows each copy: two passes over a 20-qubit state (12 KiB) 66.2 us a call
+// with it, 70.9 with a copy kernel, 69.2 with a copy and an event each. Above
+// 16 KiB it takes another route: 20 us per upload at 20 KiB, 23 at 256 KiB, 37
+// at 1 MiB, where a kernel that reads the pinned slot takes 3.5, 6 and 23 (25
+// MiB: the same 470).
+constexpr uint32_t kTinySlot = 0xFFFFFFFFu;
 struct StagedBlob {
     uint8_t *p = nullptr;
     size_t n = 0;
+    uint32_t slot = 0;
     uint8_t *data() const { return p; }
     size_t size() const { return n; }
 };
 
 int stage_blob(qw_ctx *ctx, size_t bytes, StagedBlob *out) {
-    HIP_TRY(ctx, hipEventSynchronize(ctx->staging_ev), "staging wait");
-    if (ctx->staging_cap < bytes) {
-        const size_t want = std::max(bytes, ctx->staging_cap * 2);
-        if (ctx->staging) HIP_TRY(ctx, hipHostFree(ctx->staging), "free staging");
-        ctx->staging = nullptr;
-        ctx->staging_cap = 0;
-        HIP_TRY(ctx, hipHostMalloc(&ctx->staging, want, hipHostMallocDefault), "staging alloc");
-        ctx->staging_cap = want;
-    }
-    out->p = static_cast<uint8_t *>(ctx->staging);
     out->n = bytes;
+    if (bytes <= kStageTiny) {
+        TinyRing &r = ctx->tiny;
+        const uint32_t i = r.next++ % (2 * kTinyHalf), h = i / kTinyHalf;
+        // (while recording every upload is synchronous, and the recording
+        // began with the stream's work done)
+        if (i % kTinyHalf == 0 && !ctx->rec) {
+            HIP_TRY(ctx, hipEventRecord(r.ev[h ^ 1u], ctx->stream), "staging event");
+            r.pending[h ^ 1u] = true;
+            if (r.pending[h]) HIP_TRY(ctx, hipEventSynchronize(r.ev[h]), "staging wait");
+            r.pending[h] = false;
+        }
+        out->p = r.p + (size_t)i * kStageTiny;
+        out->slot = kTinySlot;
+        return QW_OK;
+    }
+    const uint32_t slot = bytes <= kStageLarge ? ctx->stage_next++ % kStageRing : kStageRing;
+    Stage &s = ctx->stage[slot];
+    int rc = stage_wait(ctx, s, ctx->stage_done + slot * kUploadBlocks);
+    if (rc) return rc;
+    // (whole 16-byte units: the copy rounds up)
+    rc = ensure_host(ctx, s.mem, (bytes + 15) & ~size_t(15), "staging buffer");
+    if (rc) return rc;
+    out->p = static_cast<uint8_t *>(s.mem.p);
+    out->slot = slot;
     return QW_OK;
 }
 
@@ -326,10 +376,51 @@ int upload_staged(qw_ctx *ctx, const StagedBlob &b) {
         ctx->rec->plan_used = true;
         return QW_OK;
     }
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->plan.p, b.p, b.n, hipMemcpyHostToDevice, ctx->stream), "plan upload");
-    HIP_TRY(ctx, hipEventRecord(ctx->staging_ev, ctx->stream), "staging event");
+    if (b.slot == kTinySlot) {
+        HIP_TRY(ctx, hipMemcpyAsync(ctx->plan.p, b.p, b.n, hipMemcpyHostToDevice, ctx->stream), "plan upload");
+        return QW_OK;
+    }
+    Stage &s = ctx->stage[b.slot];
+    const uint32_t seq = ++ctx->stage_seq;
+    uint32_t blocks = 0;
+    HIP_TRY(ctx, launch_upload(ctx->stream, ctx->plan.p, b.p, b.n, ctx->stage_done + b.slot * kUploadBlocks, seq,
+                               &blocks),
+            "plan upload");
+    s.seq = seq;
+    s.blocks = blocks;
     return QW_OK;
 }
+
+// The context's pinned host memory and staging events.
+void free_staging(qw_ctx *ctx) {
+    if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
+    for (Stage &s : ctx->stage)
+        if (s.mem.p) (void)hipHostFree(s.mem.p);
+    if (ctx->stage_done) (void)hipHostFree(ctx->stage_done);
+    if (ctx->result.p) (void)hipHostFree(ctx->result.p);
+    if (ctx->tiny.p) (void)hipHostFree(ctx->tiny.p);
+    for (hipEvent_t e : ctx->tiny.ev)
+        if (e) (void)hipEventDestroy(e);
+}
+
+// Copy a host blob to ctx->plan (device).
+int upload(qw_ctx *ctx, const std::vector<uint8_t> &blob) {
+    if (blob.empty()) return QW_OK;
+    int rc = ensure(ctx, ctx->plan, blob.size(), "plan buffer");
+    if (rc) return rc;
+    StagedBlob s;
+    rc = stage_blob(ctx, blob.size(), &s);
+    if (rc) return rc;
+    std::memcpy(s.data(), blob.data(), blob.size());
+    return upload_staged(ctx, s);
+}
+
+// Host outputs of up to this size are written by the call's last kernel
+// straight to pinned memory and copied to the caller after the stream's
+// synchronisation (a copy to pageable memory before it takes 12 us more:
+// 23.2 against 10.9 us for a 512-byte result); larger ones go through a copy
+// of the device's.
+constexpr size_t kResultDirect = 4u << 20;
 
 // Bump layout of a blob: offsets aligned to 64 bytes.
 struct Layout {
@@ -1250,10 +1341,15 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
     if (rc) return rc;
     uint8_t *dbase = static_cast<uint8_t *>(ctx->plan.p);
     double *part = static_cast<double *>(ctx->scratch.p);
-    double *dout = out_is_host ? reinterpret_cast<double *>(
-                                     static_cast<uint8_t *>(ctx->scratch.p) +
-                                     ((part_bytes + 255) & ~size_t(255)))
-                               : out;
+    const bool direct = out_is_host && out_bytes <= kResultDirect;
+    if (direct) {
+        rc = ensure_host(ctx, ctx->result, out_bytes, "result buffer");
+        if (rc) return rc;
+    }
+    double *dout = direct ? static_cast<double *>(ctx->result.p)
+                   : out_is_host ? reinterpret_cast<double *>(static_cast<uint8_t *>(ctx->scratch.p) +
+                                                              ((part_bytes + 255) & ~size_t(255)))
+                                 : out;
     std::vector<uint8_t> blob(L.size, 0);
     std::memcpy(blob.data() + coeff_off, c, n_terms * sizeof(double));
     if (small) {
@@ -1342,9 +1438,11 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
                                            n_terms, rows, ns, dout);
     if (er != hipSuccess) return hip_fail(ctx, er, "finalize launch");
     if (out_is_host) {
-        HIP_TRY(ctx, hipMemcpyAsync(out, dout, out_bytes, hipMemcpyDeviceToHost, ctx->stream),
-                "result copy");
+        if (!direct)
+            HIP_TRY(ctx, hipMemcpyAsync(out, dout, out_bytes, hipMemcpyDeviceToHost, ctx->stream),
+                    "result copy");
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "sync");
+        if (direct) std::memcpy(out, dout, out_bytes);
     }
     return QW_OK;
 }
@@ -1496,6 +1594,14 @@ int run_measured(qw_ctx *ctx, uint32_t n, std::vector<MeasTask> &mt) {
     float *dyn = reinterpret_cast<float *>(mb + dyn_off);
     uint8_t *outc = reinterpret_cast<uint8_t *>(mb + outc_off);
     uint32_t *err = reinterpret_cast<uint32_t *>(mb + err_off);
+    if (!ctx->rec) {
+        // the outcomes and the zero-state flag go straight to host memory
+        const size_t err_at = al((size_t)total_meas);
+        rc = ensure_host(ctx, ctx->result, err_at + sizeof(uint32_t), "result buffer");
+        if (rc) return rc;
+        outc = static_cast<uint8_t *>(ctx->result.p);
+        err = reinterpret_cast<uint32_t *>(outc + err_at);
+    }
     {
         hipError_t e = launch_meas_clear(ctx->stream, err);
         if (e != hipSuccess) return hip_fail(ctx, e, "measure launch");
@@ -1620,15 +1726,9 @@ int run_measured(qw_ctx *ctx, uint32_t n, std::vector<MeasTask> &mt) {
         ctx->outcomes.clear();
         return QW_OK;
     }
-    std::vector<uint8_t> host(total_meas + sizeof(uint32_t));
-    uint32_t herr = 0;
-    if (total_meas)
-        HIP_TRY(ctx, hipMemcpyAsync(host.data(), outc, total_meas, hipMemcpyDeviceToHost, ctx->stream),
-                "outcome copy");
-    HIP_TRY(ctx, hipMemcpyAsync(&herr, err, sizeof herr, hipMemcpyDeviceToHost, ctx->stream), "outcome copy");
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "sync");
-    ctx->outcomes.assign(host.begin(), host.begin() + (std::ptrdiff_t)total_meas);
-    if (herr) return fail(ctx, QW_E_INVALID_ARG, "measurement of a zero state");
+    ctx->outcomes.assign(outc, outc + total_meas);
+    if (*err) return fail(ctx, QW_E_INVALID_ARG, "measurement of a zero state");
     (void)outc_base;
     return QW_OK;
 }
@@ -1657,14 +1757,27 @@ int qw_ctx_create(int device, void *hip_stream, qw_ctx **out) {
             ncu > 0)
             c->n_cu = (uint32_t)ncu;
     }
-    if (hipEventCreateWithFlags(&c->staging_ev, hipEventDisableTiming) != hipSuccess ||
-        hipEventRecord(c->staging_ev, c->stream) != hipSuccess || kernels_init() != hipSuccess) {
+    if (kernels_init() != hipSuccess) {
         delete c;
         return QW_E_HIP;
     }
     if (hipHostMalloc(reinterpret_cast<void **>(&c->host_flag), 2 * sizeof(uint32_t), hipHostMallocDefault) !=
         hipSuccess) {
-        hipEventDestroy(c->staging_ev);
+        delete c;
+        return QW_E_OOM;
+    }
+    const size_t done_bytes = (kStageRing + 1) * kUploadBlocks * sizeof(uint32_t);
+    if (hipHostMalloc(reinterpret_cast<void **>(&c->stage_done), done_bytes, hipHostMallocDefault) != hipSuccess) {
+        free_staging(c);
+        delete c;
+        return QW_E_OOM;
+    }
+    std::memset(c->stage_done, 0, done_bytes);   // uploads count from 1
+    if (hipHostMalloc(reinterpret_cast<void **>(&c->tiny.p), 2 * kTinyHalf * kStageTiny, hipHostMallocDefault) !=
+            hipSuccess ||
+        hipEventCreateWithFlags(&c->tiny.ev[0], hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->tiny.ev[1], hipEventDisableTiming) != hipSuccess) {
+        free_staging(c);
         delete c;
         return QW_E_OOM;
     }
@@ -1692,9 +1805,7 @@ int qw_ctx_destroy(qw_ctx *ctx) {
     if (ctx->pingpong.p) hipFree(ctx->pingpong.p);
     if (ctx->meas.p) hipFree(ctx->meas.p);
     if (ctx->psync.p) hipFree(ctx->psync.p);
-    if (ctx->host_flag) hipHostFree(ctx->host_flag);
-    if (ctx->staging) hipHostFree(ctx->staging);
-    if (ctx->staging_ev) hipEventDestroy(ctx->staging_ev);
+    free_staging(ctx);
     delete ctx;
     return QW_OK;
 }
@@ -2248,14 +2359,20 @@ int qw_sample(const qw_state *st, uint32_t first, uint32_t count, uint64_t seed,
     const size_t ss = (size_t)count * ((size_t)1 << (n - sample_sub_bits(n))) * sizeof(double);
     const size_t a1 = (cs + 255) & ~size_t(255), a2 = (tot + 255) & ~size_t(255);
     const size_t a3 = (ss + 255) & ~size_t(255);
-    rc = ensure(ctx, ctx->scratch, 2 * a1 + a2 + a3 + (out_is_host ? ob : 0) + 256, "sample scratch");
+    const bool direct = out_is_host && ob <= kResultDirect;
+    rc = ensure(ctx, ctx->scratch, 2 * a1 + a2 + a3 + (out_is_host && !direct ? ob : 0) + 256, "sample scratch");
     if (rc) return rc;
+    if (direct) {
+        rc = ensure_host(ctx, ctx->result, ob, "result buffer");
+        if (rc) return rc;
+    }
     uint8_t *sb = static_cast<uint8_t *>(ctx->scratch.p);
     double *csum = reinterpret_cast<double *>(sb);
     double *cpre = reinterpret_cast<double *>(sb + a1);
     double *total = reinterpret_cast<double *>(sb + 2 * a1);
     double *ssum = reinterpret_cast<double *>(sb + 2 * a1 + a2);
-    uint32_t *dout = out_is_host ? reinterpret_cast<uint32_t *>(sb + 2 * a1 + a2 + a3) : out;
+    uint32_t *dout = direct ? static_cast<uint32_t *>(ctx->result.p)
+                     : out_is_host ? reinterpret_cast<uint32_t *>(sb + 2 * a1 + a2 + a3) : out;
     {
         ProfScope ps(ctx, 2, (double)count * (double)(8ull << n));
         hipError_t e = launch_sample(ctx->stream, reinterpret_cast<const float2 *const *>(ctx->plan.p),
@@ -2263,8 +2380,10 @@ int qw_sample(const qw_state *st, uint32_t first, uint32_t count, uint64_t seed,
         if (e != hipSuccess) return hip_fail(ctx, e, "sample launch");
     }
     if (out_is_host) {
-        HIP_TRY(ctx, hipMemcpyAsync(out, dout, ob, hipMemcpyDeviceToHost, ctx->stream), "result copy");
+        if (!direct)
+            HIP_TRY(ctx, hipMemcpyAsync(out, dout, ob, hipMemcpyDeviceToHost, ctx->stream), "result copy");
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "sync");
+        if (direct) std::memcpy(out, dout, ob);
     }
     return QW_OK;
 }
@@ -2847,7 +2966,7 @@ void free_owned(std::vector<void *> &owned) {
 int qw_graph_begin(qw_ctx *ctx) {
     if (!ctx) return QW_E_INVALID_ARG;
     if (ctx->rec) return fail(ctx, QW_E_INVALID_ARG, "a graph is already being recorded");
-    // earlier work of the context's stream, and the staging buffer, are done
+    // earlier work of the context's stream, and its uploads, are done
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream), "stream sync");
     std::unique_ptr<GraphRec> r(new (std::nothrow) GraphRec());
     if (!r) return fail(ctx, QW_E_OOM, "host allocation");

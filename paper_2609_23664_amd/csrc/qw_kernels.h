@@ -19,6 +19,12 @@ hipError_t launch_pass(hipStream_t st, const PassDesc *d, uint32_t n_descs, uint
 // scale_out = 1/sqrt(sum norm_part) for descriptors flagged PD_NORM_OUT.
 hipError_t launch_norm_finalize(hipStream_t st, const PassDesc *d, uint32_t n_descs,
                                 uint32_t tiles);
+// Copy of `bytes` (rounded up to 16) from pinned host memory to the device,
+// by a kernel. *blocks workgroups (at most kUploadBlocks); workgroup b sets the
+// pinned word done[b] to `seq` when it has read its part of src.
+constexpr uint32_t kUploadBlocks = 64;
+hipError_t launch_upload(hipStream_t st, void *dst, const void *src, uint64_t bytes, uint32_t *done,
+                         uint32_t seq, uint32_t *blocks);
 // Every slot of [base, base + n_slots * 2^n) set to |0...0>.
 hipError_t launch_init(hipStream_t st, void *base, uint32_t n, uint32_t n_slots);
 // Device-to-device copy of `bytes` (multiple of 16).
