@@ -1040,6 +1040,9 @@ std::string jit_persist_source(const std::vector<PersistPart> &parts, int prefet
          "        if (wave == 0u) {\n"
          "            if (done_gi != kNoDep) {\n"
          "                __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"agent\");\n"
+         "                // the write-back must have finished before the counter moves: the\n"
+         "                // compiler drops the fence's own wait (it counts nothing outstanding)\n"
+         "                __builtin_amdgcn_s_waitcnt(0);\n"
          "                __hip_atomic_fetch_add(&sync[kSyncCounters + done_gi], one * done_units, __ATOMIC_RELAXED,\n"
          "                                       __HIP_MEMORY_SCOPE_AGENT);\n"
          "            }\n"
@@ -1069,6 +1072,7 @@ std::string jit_persist_source(const std::vector<PersistPart> &parts, int prefet
          "                    }\n"
          "                    // the producers' stores, released before their counter updates\n"
          "                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"agent\");\n"
+         "                    __builtin_amdgcn_s_waitcnt(0);   // before the other waves start\n"
          "                }\n"
          "            }\n"
          "            s_claim = c;   // the same value from every lane of wave 0\n"
