@@ -51,7 +51,7 @@ constexpr size_t kStageLarge = 1u << 20;
 // halves. An event behind a half's uploads is recorded when the other half is
 // entered and waited for before the half is used again.
 constexpr size_t kStageTiny = 16u << 10;
-constexpr uint32_t kTinyHalf = 16;
+constexpr uint32_t kTinyHalf = 8;
 struct TinyRing {
     uint8_t *p = nullptr;
     uint32_t next = 0;
@@ -341,6 +341,13 @@ int stage_blob(qw_ctx *ctx, size_t bytes, StagedBlob *out) {
     out->n = bytes;
     if (bytes <= kStageTiny) {
         TinyRing &r = ctx->tiny;
+        if (!r.p) {
+            for (hipEvent_t &e : r.ev)
+                if (!e) HIP_TRY(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming), "staging event");
+            HIP_TRY(ctx, hipHostMalloc(reinterpret_cast<void **>(&r.p), 2 * kTinyHalf * kStageTiny,
+                                       hipHostMallocDefault),
+                    "staging buffer");
+        }
         const uint32_t i = r.next++ % (2 * kTinyHalf), h = i / kTinyHalf;
         // (while recording every upload is synchronous, and the recording
         // began with the stream's work done)
@@ -396,7 +403,6 @@ void free_staging(qw_ctx *ctx) {
     if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
     for (Stage &s : ctx->stage)
         if (s.mem.p) (void)hipHostFree(s.mem.p);
-    if (ctx->stage_done) (void)hipHostFree(ctx->stage_done);
     if (ctx->result.p) (void)hipHostFree(ctx->result.p);
     if (ctx->tiny.p) (void)hipHostFree(ctx->tiny.p);
     for (hipEvent_t e : ctx->tiny.ev)
@@ -1761,26 +1767,15 @@ int qw_ctx_create(int device, void *hip_stream, qw_ctx **out) {
         delete c;
         return QW_E_HIP;
     }
-    if (hipHostMalloc(reinterpret_cast<void **>(&c->host_flag), 2 * sizeof(uint32_t), hipHostMallocDefault) !=
-        hipSuccess) {
-        delete c;
-        return QW_E_OOM;
-    }
+    // one pinned block: abandon flags, then the upload words
     const size_t done_bytes = (kStageRing + 1) * kUploadBlocks * sizeof(uint32_t);
-    if (hipHostMalloc(reinterpret_cast<void **>(&c->stage_done), done_bytes, hipHostMallocDefault) != hipSuccess) {
-        free_staging(c);
+    if (hipHostMalloc(reinterpret_cast<void **>(&c->host_flag), 2 * sizeof(uint32_t) + done_bytes,
+                      hipHostMallocDefault) != hipSuccess) {
         delete c;
         return QW_E_OOM;
     }
+    c->stage_done = c->host_flag + 2;
     std::memset(c->stage_done, 0, done_bytes);   // uploads count from 1
-    if (hipHostMalloc(reinterpret_cast<void **>(&c->tiny.p), 2 * kTinyHalf * kStageTiny, hipHostMallocDefault) !=
-            hipSuccess ||
-        hipEventCreateWithFlags(&c->tiny.ev[0], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->tiny.ev[1], hipEventDisableTiming) != hipSuccess) {
-        free_staging(c);
-        delete c;
-        return QW_E_OOM;
-    }
     __atomic_store_n(&c->host_flag[0], 0u, __ATOMIC_RELAXED);
     __atomic_store_n(&c->host_flag[1], 0u, __ATOMIC_RELAXED);
     *out = c;
