@@ -3,8 +3,9 @@
 // Layout: a state slot is 2^n complex64 amplitudes (float2, interleaved),
 // qubit q = bit q of the index.
 //
-// Gate pass (pass_kernel<M>): one workgroup owns one tile of 2^M amplitudes
-// per (task, pass); the tile is the set of indices that differ only in the
+// Gate pass (pass_kernel_lds, pass_kernel_flat): one workgroup (several in
+// the flat form) owns one tile of 2^M amplitudes per (task, pass); the tile
+// is the set of indices that differ only in the
 // pass's M local bits. 2^(M-4) threads hold 16 amplitudes each in registers.
 // A "phase" maps 4 local bits to the 16 register slots and the remaining
 // M-4 local bits to the thread index (its 6 lowest bits to the lanes of a
@@ -83,157 +84,180 @@ __device__ __forceinline__ bool opbit_tg(uint8_t loc, uint8_t bit, uint32_t tl, 
     return loc == LOC_THREAD ? ((tl >> bit) & 1u) : ((uint32_t)(base >> bit) & 1u);
 }
 
+// The 16 amplitudes as one value. An operation takes them out into an array,
+// works on that with constant indices and puts them back: passed by reference
+// through the switch over the operations, the array's addresses are merged by
+// the compiler before it can split the array into registers, and every
+// operation then loads and stores it in scratch memory. 4 layers on one
+// 15-qubit state took 587 us that way, 128 now; 2 layers on 64 20-qubit states
+// 8.05 ms, now 1.51; on 8 24-qubit states 20.7 ms, now 3.39.
+typedef float Amps __attribute__((ext_vector_type(32)));
+
+template <class F>
+__device__ __forceinline__ Amps on(Amps r, F &&f) {
+    float2 v[16];
+    #pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = make_float2(r[2 * k], r[2 * k + 1]);
+    f(v);
+    #pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        r[2 * k] = v[k].x;
+        r[2 * k + 1] = v[k].y;
+    }
+    return r;
+}
+
+#define QW_ON(CALL) r = on(r, [&](float2 (&v)[16]) __attribute__((always_inline)) { CALL; })
 #define QW_SLOT4(FN, SEL, ...)                                    \
     switch (SEL) {                                                \
-    case 0: FN<0>(__VA_ARGS__); break;                            \
-    case 1: FN<1>(__VA_ARGS__); break;                            \
-    case 2: FN<2>(__VA_ARGS__); break;                            \
-    default: FN<3>(__VA_ARGS__); break;                           \
+    case 0: QW_ON(FN<0>(v, __VA_ARGS__)); break;                  \
+    case 1: QW_ON(FN<1>(v, __VA_ARGS__)); break;                  \
+    case 2: QW_ON(FN<2>(v, __VA_ARGS__)); break;                  \
+    default: QW_ON(FN<3>(v, __VA_ARGS__)); break;                 \
     }
 #define QW_LANE6(FN, SEL, ...)                                    \
     switch (SEL) {                                                \
-    case 0: FN<0>(__VA_ARGS__); break;                            \
-    case 1: FN<1>(__VA_ARGS__); break;                            \
-    case 2: FN<2>(__VA_ARGS__); break;                            \
-    case 3: FN<3>(__VA_ARGS__); break;                            \
-    case 4: FN<4>(__VA_ARGS__); break;                            \
-    default: FN<5>(__VA_ARGS__); break;                           \
+    case 0: QW_ON(FN<0>(v, __VA_ARGS__)); break;                  \
+    case 1: QW_ON(FN<1>(v, __VA_ARGS__)); break;                  \
+    case 2: QW_ON(FN<2>(v, __VA_ARGS__)); break;                  \
+    case 3: QW_ON(FN<3>(v, __VA_ARGS__)); break;                  \
+    case 4: QW_ON(FN<4>(v, __VA_ARGS__)); break;                  \
+    default: QW_ON(FN<5>(v, __VA_ARGS__)); break;                 \
     }
-
-// CX / CZ with a register control slot chosen at run time.
-template <int S>
-__device__ __forceinline__ void cx_rr_s(float2 (&v)[16], uint32_t c) {
-    switch (c) {
-    case 0: cx_rr<S, 0>(v); break;
-    case 1: cx_rr<S, 1>(v); break;
-    case 2: cx_rr<S, 2>(v); break;
-    default: cx_rr<S, 3>(v); break;
+// a pair of slots (a target, or one operand of a CZ, and a control)
+#define QW_SLOT4C(FN, S, C)                                       \
+    switch (C) {                                                  \
+    case 0: QW_ON((FN<S, 0>(v))); break;                          \
+    case 1: QW_ON((FN<S, 1>(v))); break;                          \
+    case 2: QW_ON((FN<S, 2>(v))); break;                          \
+    default: QW_ON((FN<S, 3>(v))); break;                         \
     }
-}
-template <int J>
-__device__ __forceinline__ void cx_lr_s(float2 (&v)[16], uint32_t c) {
-    switch (c) {
-    case 0: cx_lr<J, 0>(v); break;
-    case 1: cx_lr<J, 1>(v); break;
-    case 2: cx_lr<J, 2>(v); break;
-    default: cx_lr<J, 3>(v); break;
+#define QW_URT4(F, SEL, T)                                        \
+    switch (SEL) {                                                \
+    case 0: QW_ON((urt_r<0, F>(v, T))); break;                    \
+    case 1: QW_ON((urt_r<1, F>(v, T))); break;                    \
+    case 2: QW_ON((urt_r<2, F>(v, T))); break;                    \
+    default: QW_ON((urt_r<3, F>(v, T))); break;                   \
     }
-}
-template <int S>
-__device__ __forceinline__ void cz_rr_s(float2 (&v)[16], uint32_t c) {
-    switch (c) {
-    case 0: cz_rr<S, 0>(v); break;
-    case 1: cz_rr<S, 1>(v); break;
-    case 2: cz_rr<S, 2>(v); break;
-    default: cz_rr<S, 3>(v); break;
+#define QW_URT6(F, SEL, T)                                        \
+    switch (SEL) {                                                \
+    case 0: QW_ON((urt_l<0, F>(v, T, lane))); break;              \
+    case 1: QW_ON((urt_l<1, F>(v, T, lane))); break;              \
+    case 2: QW_ON((urt_l<2, F>(v, T, lane))); break;              \
+    case 3: QW_ON((urt_l<3, F>(v, T, lane))); break;              \
+    case 4: QW_ON((urt_l<4, F>(v, T, lane))); break;              \
+    default: QW_ON((urt_l<5, F>(v, T, lane))); break;             \
     }
-}
-
-template <int F>
-__device__ __forceinline__ void urt_r_s(float2 (&v)[16], uint32_t slot, float t) {
-    switch (slot) {
-    case 0: urt_r<0, F>(v, t); break;
-    case 1: urt_r<1, F>(v, t); break;
-    case 2: urt_r<2, F>(v, t); break;
-    default: urt_r<3, F>(v, t); break;
-    }
-}
-template <int F>
-__device__ __forceinline__ void urt_l_s(float2 (&v)[16], uint32_t j, float t, uint32_t lane) {
-    switch (j) {
-    case 0: urt_l<0, F>(v, t, lane); break;
-    case 1: urt_l<1, F>(v, t, lane); break;
-    case 2: urt_l<2, F>(v, t, lane); break;
-    case 3: urt_l<3, F>(v, t, lane); break;
-    case 4: urt_l<4, F>(v, t, lane); break;
-    default: urt_l<5, F>(v, t, lane); break;
-    }
-}
 
 // One op record (not OP_DSET) on the registers of a phase.
-__device__ __forceinline__ void run_op(float2 (&v)[16], const DevOp &op, const DevOp *ops,
-                                       uint32_t j, uint32_t tl, uint64_t base) {
+__device__ __forceinline__ Amps run_op(Amps r, const DevOp &op, const DevOp *ops, uint32_t j,
+                                       uint32_t tl, uint64_t base) {
     const uint32_t lane = threadIdx.x & 63u;
     if (op.la == LOC_LANE) {
         switch (op.type) {
         case OP_U:
-            QW_LANE6(u_l, op.sa, v, opc(ops, j, 0), opc(ops, j, 1), opc(ops, j, 2), opc(ops, j, 3), lane)
-            return;
+            QW_LANE6(u_l, op.sa, opc(ops, j, 0), opc(ops, j, 1), opc(ops, j, 2), opc(ops, j, 3), lane)
+            break;
         case OP_UR:
-            QW_LANE6(ur_l, op.sa, v, opm(ops, j, 0), opm(ops, j, 1), opm(ops, j, 2), opm(ops, j, 3), lane)
-            return;
+            QW_LANE6(ur_l, op.sa, opm(ops, j, 0), opm(ops, j, 1), opm(ops, j, 2), opm(ops, j, 3), lane)
+            break;
         case OP_URD: {
             const Urd e = urd_entries(ops, j);
-            QW_LANE6(ur_l, op.sa, v, e.a, e.b, e.c, e.d, lane)
-            return;
+            QW_LANE6(ur_l, op.sa, e.a, e.b, e.c, e.d, lane)
+            break;
         }
         case OP_URT:
-            if (op.b) urt_l_s<1>(v, op.sa, opm(ops, j, 0), lane);
-            else urt_l_s<0>(v, op.sa, opm(ops, j, 0), lane);
-            return;
+            if (op.b) {
+                QW_URT6(1, op.sa, opm(ops, j, 0))
+            } else {
+                QW_URT6(0, op.sa, opm(ops, j, 0))
+            }
+            break;
         case OP_PERM:
-            QW_LANE6(perm_l, op.sa, v, opc(ops, j, 0), opc(ops, j, 1), lane)
-            return;
+            QW_LANE6(perm_l, op.sa, opc(ops, j, 0), opc(ops, j, 1), lane)
+            break;
         case OP_CX:
             if (op.lb == LOC_REG) {
-                QW_LANE6(cx_lr_s, op.sa, v, op.sb)
+                switch (op.sa) {
+                case 0: QW_SLOT4C(cx_lr, 0, op.sb) break;
+                case 1: QW_SLOT4C(cx_lr, 1, op.sb) break;
+                case 2: QW_SLOT4C(cx_lr, 2, op.sb) break;
+                case 3: QW_SLOT4C(cx_lr, 3, op.sb) break;
+                case 4: QW_SLOT4C(cx_lr, 4, op.sb) break;
+                default: QW_SLOT4C(cx_lr, 5, op.sb) break;
+                }
             } else {
                 const bool c = opbit_tg(op.lb, op.b, tl, base);
-                QW_LANE6(cx_lb, op.sa, v, c)
+                QW_LANE6(cx_lb, op.sa, c)
             }
-            return;
-        default: return;
+            break;
+        default: break;
         }
+        return r;
     }
     switch (op.type) {
     case OP_URT:
-        if (op.b) urt_r_s<1>(v, op.sa, opm(ops, j, 0));
-        else urt_r_s<0>(v, op.sa, opm(ops, j, 0));
+        if (op.b) {
+            QW_URT4(1, op.sa, opm(ops, j, 0))
+        } else {
+            QW_URT4(0, op.sa, opm(ops, j, 0))
+        }
         break;
     case OP_UR:
-        QW_SLOT4(ur_r, op.sa, v, opm(ops, j, 0), opm(ops, j, 1), opm(ops, j, 2), opm(ops, j, 3))
+        QW_SLOT4(ur_r, op.sa, opm(ops, j, 0), opm(ops, j, 1), opm(ops, j, 2), opm(ops, j, 3))
         break;
     case OP_URD: {
         const Urd e = urd_entries(ops, j);
-        QW_SLOT4(ur_r, op.sa, v, e.a, e.b, e.c, e.d)
+        QW_SLOT4(ur_r, op.sa, e.a, e.b, e.c, e.d)
         break;
     }
     case OP_U:
-        QW_SLOT4(u_r, op.sa, v, opc(ops, j, 0), opc(ops, j, 1), opc(ops, j, 2), opc(ops, j, 3))
+        QW_SLOT4(u_r, op.sa, opc(ops, j, 0), opc(ops, j, 1), opc(ops, j, 2), opc(ops, j, 3))
         break;
     case OP_PERM:
-        QW_SLOT4(perm_r, op.sa, v, opc(ops, j, 0), opc(ops, j, 1))
+        QW_SLOT4(perm_r, op.sa, opc(ops, j, 0), opc(ops, j, 1))
         break;
     case OP_CX:
         if (op.lb == LOC_REG) {
-            QW_SLOT4(cx_rr_s, op.sa, v, op.sb)
+            switch (op.sa) {
+            case 0: QW_SLOT4C(cx_rr, 0, op.sb) break;
+            case 1: QW_SLOT4C(cx_rr, 1, op.sb) break;
+            case 2: QW_SLOT4C(cx_rr, 2, op.sb) break;
+            default: QW_SLOT4C(cx_rr, 3, op.sb) break;
+            }
         } else {
             const bool c = opbit_tg(op.lb, op.b, tl, base);
-            QW_SLOT4(cx_rb, op.sa, v, c)
+            QW_SLOT4(cx_rb, op.sa, c)
         }
         break;
     case OP_DIAG:
         if (op.la == LOC_REG) {
-            QW_SLOT4(diag_r, op.sa, v, opc(ops, j, 0), opc(ops, j, 1))
+            QW_SLOT4(diag_r, op.sa, opc(ops, j, 0), opc(ops, j, 1))
         } else {
-            diag_b(v, opbit_tg(op.la, op.a, tl, base), opc(ops, j, 0), opc(ops, j, 1));
+            QW_ON(diag_b(v, opbit_tg(op.la, op.a, tl, base), opc(ops, j, 0), opc(ops, j, 1)));
         }
         break;
     case OP_CZ:
         if (op.la == LOC_REG && op.lb == LOC_REG) {
-            QW_SLOT4(cz_rr_s, op.sa, v, op.sb)
+            switch (op.sa) {
+            case 0: QW_SLOT4C(cz_rr, 0, op.sb) break;
+            case 1: QW_SLOT4C(cz_rr, 1, op.sb) break;
+            case 2: QW_SLOT4C(cz_rr, 2, op.sb) break;
+            default: QW_SLOT4C(cz_rr, 3, op.sb) break;
+            }
         } else if (op.la == LOC_REG) {
             const bool c = opbit_tg(op.lb, op.b, tl, base);
-            QW_SLOT4(cz_rb, op.sa, v, c)
+            QW_SLOT4(cz_rb, op.sa, c)
         } else if (op.lb == LOC_REG) {
             const bool c = opbit_tg(op.la, op.a, tl, base);
-            QW_SLOT4(cz_rb, op.sb, v, c)
+            QW_SLOT4(cz_rb, op.sb, c)
         } else {
-            cz_bb(v, opbit_tg(op.la, op.a, tl, base) && opbit_tg(op.lb, op.b, tl, base));
+            QW_ON(cz_bb(v, opbit_tg(op.la, op.a, tl, base) && opbit_tg(op.lb, op.b, tl, base)));
         }
         break;
     default: break;
     }
+    return r;
 }
 
 // ------------------------------------------------------------- pass kernel
@@ -331,39 +355,68 @@ __device__ __forceinline__ IoLayout io_out_layout(const PassDesc &d, uint32_t ti
     return io;
 }
 
-__device__ __forceinline__ void io_load(float2 (&v)[16], const void *src, const IoLayout &io,
-                                        uint8_t kind) {
+__device__ __forceinline__ Amps io_load(const void *src, const IoLayout &io, uint8_t kind) {
     const uint32_t lb = io.lane_off * 8u;
+    Amps r;
     if (kind == IO_F4) {
         #pragma unroll
         for (int k2 = 0; k2 < 8; ++k2) {
             const float4 q = buf_ld4(src, io.uni_off[2 * k2], lb);
-            v[2 * k2] = make_float2(q.x, q.y);
-            v[2 * k2 + 1] = make_float2(q.z, q.w);
+            r[4 * k2] = q.x;
+            r[4 * k2 + 1] = q.y;
+            r[4 * k2 + 2] = q.z;
+            r[4 * k2 + 3] = q.w;
         }
     } else {
         #pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = buf_ld2(src, io.uni_off[k], lb);
+        for (int k = 0; k < 16; ++k) {
+            const float2 q = buf_ld2(src, io.uni_off[k], lb);
+            r[2 * k] = q.x;
+            r[2 * k + 1] = q.y;
+        }
     }
+    return r;
 }
 
-__device__ __forceinline__ void io_store(const float2 (&v)[16], void *dst, const IoLayout &io,
-                                         uint8_t kind) {
+__device__ __forceinline__ void io_store(Amps r, void *dst, const IoLayout &io, uint8_t kind) {
     const uint32_t lb = io.lane_off * 8u;
     if (kind == IO_F4) {
         #pragma unroll
-        for (int k2 = 0; k2 < 8; ++k2) buf_st4(dst, io.uni_off[2 * k2], lb, v[2 * k2], v[2 * k2 + 1]);
+        for (int k2 = 0; k2 < 8; ++k2)
+            buf_st4(dst, io.uni_off[2 * k2], lb, make_float2(r[4 * k2], r[4 * k2 + 1]),
+                    make_float2(r[4 * k2 + 2], r[4 * k2 + 3]));
     } else {
         #pragma unroll
-        for (int k = 0; k < 16; ++k) buf_st2(dst, io.uni_off[k], lb, v[k]);
+        for (int k = 0; k < 16; ++k) buf_st2(dst, io.uni_off[k], lb, make_float2(r[2 * k], r[2 * k + 1]));
     }
+}
+
+// block_sum of a workgroup of `waves` waves.
+__device__ double block_sum_n(double v, double *red, uint32_t waves) {
+    #pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (waves == 1u) return v;
+    __syncthreads();
+    if ((threadIdx.x & 63u) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x == 0)
+        for (uint32_t k = 0; k < waves; ++k) s += red[k];
+    return s;
+}
+
+// Amplitudes scaled in FP64 (PD_SCALE_IN).
+__device__ __forceinline__ Amps scale_in(Amps r, double s) {
+    #pragma unroll
+    for (int k = 0; k < 32; ++k) r[k] = (float)((double)r[k] * s);
+    return r;
 }
 
 // Run the ops of one op range [o, end) on the registers. The next op record
 // is requested before the current one is executed (scalar-load prefetch).
-__device__ __forceinline__ void run_ops(float2 (&v)[16], const DevOp *ops, uint32_t o,
-                                        uint32_t end, uint32_t tl, uint64_t base) {
-    if (o >= end) return;
+__device__ __forceinline__ Amps run_ops(Amps r, const DevOp *ops, uint32_t o, uint32_t end,
+                                        uint32_t tl, uint64_t base) {
+    if (o >= end) return r;
     DevOp nxt = ld_words(ops + o);
     while (o < end) {
         const DevOp op = nxt;
@@ -383,114 +436,89 @@ __device__ __forceinline__ void run_ops(float2 (&v)[16], const DevOp *ops, uint3
             const uint32_t merged = (op.a && (op.sb || op.b)) ? 1u : 0u;
             if (merged) {
                 const DevOp mm = ld_words(ops + m0 + op.b);
-                dset_apply_m(v, op.sb ? ops + o + 1 : ops, op.sb != 0, ft,
-                             pdiag_tg(tl, base, mm.tmask, mm.gmask), opc(ops, m0 + op.b, 0),
-                             opc(ops, m0 + op.b, 1), mm.rmask);
+                const bool pt = pdiag_tg(tl, base, mm.tmask, mm.gmask);
+                const float2 d0 = opc(ops, m0 + op.b, 0), d1 = opc(ops, m0 + op.b, 1);
+                if (op.sb) {
+                    QW_ON(dset_apply_m(v, ops + o + 1, true, ft, pt, d0, d1, mm.rmask));
+                } else {
+                    QW_ON(dset_apply_m(v, ops, false, ft, pt, d0, d1, mm.rmask));
+                }
             } else if (op.sb) {
-                dset_apply(v, ops + o + 1, true, ft, op.b != 0);
+                if (op.b) {
+                    QW_ON(dset_apply(v, ops + o + 1, true, ft, true));
+                } else {
+                    QW_ON(dset_apply(v, ops + o + 1, true, ft, false));
+                }
             } else if (op.b) {
-                dset_apply(v, ops, false, ft, true);
+                QW_ON(dset_apply(v, ops, false, ft, true));
             }
             for (uint32_t j = merged; j < op.a; ++j) {
                 const DevOp mm = ld_words(ops + m0 + op.b + j);
-                pdiag_mixed(v, pdiag_tg(tl, base, mm.tmask, mm.gmask), opc(ops, m0 + op.b + j, 0),
-                            opc(ops, m0 + op.b + j, 1), mm.rmask);
+                const bool pt = pdiag_tg(tl, base, mm.tmask, mm.gmask);
+                const float2 d0 = opc(ops, m0 + op.b + j, 0), d1 = opc(ops, m0 + op.b + j, 1);
+                QW_ON(pdiag_mixed(v, pt, d0, d1, mm.rmask));
             }
         } else {
-            run_op(v, op, ops, o, tl, base);
+            r = run_op(r, op, ops, o, tl, base);
         }
         o += step;
     }
+    return r;
 }
 
-template <int M>
-__global__ __launch_bounds__((1 << (M - 4)) < 256 ? (1 << (M - 4)) : 256)
-void pass_kernel_flat(const PassDesc *__restrict__ descs, uint32_t n_descs, uint32_t n,
-                      uint32_t items, int remap) {
-    constexpr int T = 1 << (M - 4);
-    constexpr int WG = T < 256 ? T : 256;
-    constexpr int PARTS = T / WG;
+// (The tile size is a run-time argument of both forms: it only sets the
+// workgroup size and the LDS bytes.) One-phase passes: workgroups of at most
+// 256 threads, several per tile.
+__global__ __launch_bounds__(256) void pass_kernel_flat(const PassDesc *__restrict__ descs, uint32_t n_descs,
+                                                        uint32_t parts, uint32_t items, int remap) {
     const uint32_t wg_item = item_of(blockIdx.x, gridDim.x, remap);
-    const uint32_t item = wg_item / PARTS;
+    const uint32_t item = wg_item / parts;
     if (item >= items) return;
-    const uint32_t part = wg_item % PARTS;
+    const uint32_t part = wg_item % parts;
     const uint32_t p = item % n_descs;
     const uint32_t tile = item / n_descs;
     const PassDesc d = ld_words(descs + p);
     const uint32_t base = uni(ldu(d.tile_base + tile));
-    const uint32_t tid = part * WG + threadIdx.x;
+    const uint32_t tid = part * blockDim.x + threadIdx.x;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = uni(tid >> 6);
-    float2 v[16];
     const PhaseHead ph = ld_phase_head(d.phases);
     const uint32_t tl = thread_local_index(tid, ph.reg);
-    const IoLayout io = io_from_rec(d.io_in, lane, wave, base);
-    io_load(v, d.src, io, ph.io);
-    if (d.flags & PD_SCALE_IN) {
-        const double s = *gin<double>(d.scale_in);
-        #pragma unroll
-        for (int k = 0; k < 16; ++k)
-            v[k] = make_float2((float)((double)v[k].x * s), (float)((double)v[k].y * s));
-    }
-    run_ops(v, d.ops, ph.op_begin, ph.op_end, tl, base);
-    io_store(v, d.dst, io_out_layout(d, tile, lane, wave, base), ph.io);
+    Amps r = io_load(d.src, io_from_rec(d.io_in, lane, wave, base), ph.io);
+    if (d.flags & PD_SCALE_IN) r = scale_in(r, *gin<double>(d.scale_in));
+    r = run_ops(r, d.ops, ph.op_begin, ph.op_end, tl, base);
+    io_store(r, d.dst, io_out_layout(d, tile, lane, wave, base), ph.io);
 }
 
-// Multi-phase passes: one 1024-thread workgroup per CU owns a whole tile in
-// LDS for exchanges. Workgroups are persistent: each walks a list of items
-// and loads the next tile into registers before working on the current one,
-// so HBM traffic overlaps the exchanges and arithmetic. The items of XCD x
-// (workgroups b with b mod 8 == x) are one contiguous range, so the tasks
-// that read the same snapshot tile run on one XCD at about the same time.
-template <int M>
-__global__ __launch_bounds__(1 << (M - 4)) void pass_kernel_lds(const PassDesc *__restrict__ descs,
-                                                                uint32_t n_descs, uint32_t n,
-                                                                uint32_t items) {
-    constexpr int T = 1 << (M - 4);
-    __shared__ float2 lds[1 << M];
-    __shared__ double red[T / 64 + 1];
+// Multi-phase passes: a workgroup of up to 1024 threads owns a whole tile in
+// LDS for exchanges. Workgroups are persistent: each walks a list of items.
+// The items of XCD x (workgroups b with b mod 8 == x) are one contiguous
+// range, so the tasks that read the same snapshot tile run on one XCD at about
+// the same time. Bound by the operations' issue, not by memory, so the next
+// tile is not loaded ahead.
+__global__ __launch_bounds__(1024) void pass_kernel_lds(const PassDesc *__restrict__ descs,
+                                                        uint32_t n_descs, uint32_t items) {
+    extern __shared__ float2 lds[];   // one tile: 16 amplitudes per thread
+    __shared__ double red[17];
     const uint32_t w = blockIdx.x, x = w & 7u, j = w >> 3, wpx = gridDim.x >> 3;
     const uint32_t per = (items + 7u) >> 3;
     const uint32_t first = x * per;
     const uint32_t last = (first + per < items) ? first + per : items;
     uint32_t item = first + j;
     if (item >= last) return;
-    const uint64_t full = (n >= 64) ? ~0ull : ((1ull << n) - 1ull);
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
     const uint32_t wave = uni(tid >> 6);
     char *lb = reinterpret_cast<char *>(lds);
 
-    float2 nv[16];
-    {
-        const PassDesc d0 = ld_words(descs + item % n_descs);
-        const uint32_t base0 = uni(ldu(d0.tile_base + item / n_descs));
-        const IoLayout io0 = io_from_rec(d0.io_in, lane, wave, base0);
-        io_load(nv, d0.src, io0, ld_phase_head(d0.phases).io);
-    }
     while (true) {
-        float2 v[16];
-        #pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = nv[k];
         const uint32_t p = item % n_descs;
         const uint32_t tile = item / n_descs;
         const PassDesc d = ld_words(descs + p);
         const uint32_t base = uni(ldu(d.tile_base + tile));
-        const uint32_t next = item + wpx;
-        const bool has_next = next < last;
-        if (has_next) {
-            const PassDesc dn = ld_words(descs + next % n_descs);
-            const uint32_t basen = uni(ldu(dn.tile_base + next / n_descs));
-            const IoLayout ion = io_from_rec(dn.io_in, lane, wave, basen);
-            io_load(nv, dn.src, ion, ld_phase_head(dn.phases).io);
-        }
-        if (d.flags & PD_SCALE_IN) {
-            const double s = *gin<double>(d.scale_in);
-            #pragma unroll
-            for (int k = 0; k < 16; ++k)
-                v[k] = make_float2((float)((double)v[k].x * s), (float)((double)v[k].y * s));
-        }
         PhaseHead ph = ld_phase_head(d.phases);
+        Amps r = io_load(d.src, io_from_rec(d.io_in, lane, wave, base), ph.io);
+        if (d.flags & PD_SCALE_IN) r = scale_in(r, *gin<double>(d.scale_in));
         uint32_t tl = thread_local_index(tid, ph.reg);
         const uint32_t nph = d.n_phases;
         for (uint32_t pi = 0; pi < nph; ++pi) {
@@ -501,31 +529,34 @@ __global__ __launch_bounds__(1 << (M - 4)) void pass_kernel_lds(const PassDesc *
                 lds_barrier();
                 #pragma unroll
                 for (int k = 0; k < 16; ++k)
-                    *reinterpret_cast<float2 *>(lb + (stl8 ^ uni(ldu(off_prev + k)))) = v[k];
+                    *reinterpret_cast<float2 *>(lb + (stl8 ^ uni(ldu(off_prev + k)))) =
+                        make_float2(r[2 * k], r[2 * k + 1]);
                 lds_barrier();
                 ph = ld_phase_head(d.phases + pi);
                 tl = thread_local_index(tid, ph.reg);
                 const uint32_t ntl8 = swz(tl) << 3;
                 #pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    v[k] = *reinterpret_cast<const float2 *>(lb + (ntl8 ^ uni(ldu(off_next + k))));
+                for (int k = 0; k < 16; ++k) {
+                    const float2 q = *reinterpret_cast<const float2 *>(lb + (ntl8 ^ uni(ldu(off_next + k))));
+                    r[2 * k] = q.x;
+                    r[2 * k + 1] = q.y;
+                }
             }
-            run_ops(v, d.ops, ph.op_begin, ph.op_end, tl, base);
+            r = run_ops(r, d.ops, ph.op_begin, ph.op_end, tl, base);
         }
         if (d.flags & PD_NORM_OUT) {
             double s = 0.0;
             #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const double xx = v[k].x, yy = v[k].y;
-                s = fma(xx, xx, s);
-                s = fma(yy, yy, s);
+            for (int k = 0; k < 32; ++k) {
+                const double x = r[k];
+                s = fma(x, x, s);
             }
-            s = block_sum<T>(s, red);
+            s = block_sum_n(s, red, blockDim.x >> 6);
             if (tid == 0) gout<double>(d.norm_part)[tile] = s;
         }
-        io_store(v, d.dst, io_out_layout(d, tile, lane, wave, base), ph.io);
-        if (!has_next) break;
-        item = next;
+        io_store(r, d.dst, io_out_layout(d, tile, lane, wave, base), ph.io);
+        item += wpx;
+        if (item >= last) break;
         lds_barrier();  // the next tile's first exchange reuses the LDS buffer
     }
 }
@@ -760,7 +791,9 @@ __global__ __launch_bounds__(1 << (M - 4)) void reduce_kernel(const ReduceDesc *
             {
                 const uint32_t tl = thread_local_index(tid, io);
                 const IoLayout lay = io_layout(lmask, io, IO_F4, lane, uni(tid >> 6), M, (uint32_t)base);
-                io_load(v, d.psi, lay, IO_F4);
+                const Amps r = io_load(d.psi, lay, IO_F4);
+                #pragma unroll
+                for (int k2 = 0; k2 < 16; ++k2) v[k2] = make_float2(r[2 * k2], r[2 * k2 + 1]);
                 __syncthreads();   // the previous tile's LDS reads are done
                 const uint32_t stl8 = swz(tl) << 3;
                 char *lb = reinterpret_cast<char *>(lds);
@@ -1405,31 +1438,6 @@ __global__ __launch_bounds__(256) void draw_kernel(const float2 *const *__restri
 // ------------------------------------------------------------- launchers
 static_assert(sizeof(float2) == 8, "float2");
 
-template <int M>
-static hipError_t launch_pass_m(hipStream_t st, const PassDesc *d, uint32_t n_descs, uint32_t n,
-                                uint32_t tiles, int remap, bool use_lds, uint32_t n_cu) {
-    const uint64_t items64 = (uint64_t)n_descs * tiles;
-    if (items64 == 0) return hipSuccess;
-    constexpr int T = 1 << (M - 4);
-    constexpr int WG_FLAT = T < 256 ? T : 256;
-    if (items64 * (T / WG_FLAT) > 0x7FFFFFF8ull) return hipErrorInvalidValue;
-    const uint32_t items = (uint32_t)items64;
-    if (use_lds) {
-        // one persistent workgroup per CU (a multiple of 8 for the XCD split)
-        uint32_t grid = n_cu;
-        const uint32_t need = ((items + 7u) / 8u) * 8u;
-        if (need < grid) grid = need;
-        grid = ((grid + 7u) / 8u) * 8u;
-        hipLaunchKernelGGL(pass_kernel_lds<M>, dim3(grid), dim3(T), 0, st, d, n_descs, n, items);
-    } else {
-        uint32_t grid = (uint32_t)(items64 * (T / WG_FLAT));
-        if (remap) grid = ((grid + 7u) / 8u) * 8u;
-        hipLaunchKernelGGL(pass_kernel_flat<M>, dim3(grid), dim3(WG_FLAT), 0, st, d, n_descs, n,
-                           items, remap);
-    }
-    return hipGetLastError();
-}
-
 static uint32_t cu_count() {
     static uint32_t cached = 0;
     if (cached) return cached;
@@ -1450,16 +1458,24 @@ hipError_t launch_pass(hipStream_t st, const PassDesc *d, uint32_t n_descs, uint
         hipLaunchKernelGGL(small_pass_kernel, dim3(n_descs), dim3(64), 0, st, d, n);
         return hipGetLastError();
     }
-    const uint32_t tiles = 1u << (n - m);
-    const uint32_t ncu = cu_count();
-    switch (m) {
-    case 10: return launch_pass_m<10>(st, d, n_descs, n, tiles, remap, use_lds, ncu);
-    case 11: return launch_pass_m<11>(st, d, n_descs, n, tiles, remap, use_lds, ncu);
-    case 12: return launch_pass_m<12>(st, d, n_descs, n, tiles, remap, use_lds, ncu);
-    case 13: return launch_pass_m<13>(st, d, n_descs, n, tiles, remap, use_lds, ncu);
-    case 14: return launch_pass_m<14>(st, d, n_descs, n, tiles, remap, use_lds, ncu);
-    default: return hipErrorInvalidValue;
+    if (m > (uint32_t)kMaxTileBits) return hipErrorInvalidValue;
+    const uint64_t items64 = (uint64_t)n_descs << (n - m);
+    const uint32_t T = 1u << (m - 4), wg = T < 256 ? T : 256, parts = T / wg;
+    if (items64 * parts > 0x7FFFFFF8ull) return hipErrorInvalidValue;
+    const uint32_t items = (uint32_t)items64;
+    if (use_lds) {
+        // one persistent workgroup per CU, more of smaller tiles (a multiple
+        // of 8 for the XCD split)
+        const uint32_t full = cu_count() * (1024u / T < 8u ? 1024u / T : 8u);
+        const uint32_t need = ((items + 7u) / 8u) * 8u;
+        const uint32_t grid = ((std::min(full, need) + 7u) / 8u) * 8u;
+        hipLaunchKernelGGL(pass_kernel_lds, dim3(grid), dim3(T), sizeof(float2) << m, st, d, n_descs, items);
+    } else {
+        uint32_t grid = items * parts;
+        if (remap) grid = ((grid + 7u) / 8u) * 8u;
+        hipLaunchKernelGGL(pass_kernel_flat, dim3(grid), dim3(wg), 0, st, d, n_descs, parts, items, remap);
     }
+    return hipGetLastError();
 }
 
 hipError_t launch_norm_finalize(hipStream_t st, const PassDesc *d, uint32_t n_descs,
