@@ -918,6 +918,14 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
     std::vector<std::vector<Group>> groups(steps);
     const bool use_jit = ctx->jit && m >= kMinTileBits;
     std::vector<JitReq> reqs;
+    // the states that the call reads and writes, for the cache policies
+    std::vector<const void *> swept;
+    for (size_t t = 0; t < ex.size(); ++t)
+        for (const void *s : {(const void *)ex[t].src, (const void *)ex[t].dst, (const void *)second[t]})
+            if (s) swept.push_back(s);
+    std::sort(swept.begin(), swept.end());
+    swept.erase(std::unique(swept.begin(), swept.end()), swept.end());
+    const bool fits = swept.size() * state_bytes <= kIoCacheBytes;
     if (use_jit) {
         std::vector<std::vector<std::pair<size_t, std::vector<size_t>>>> members(steps);
         for (size_t k = 0; k < steps; ++k) {
@@ -927,12 +935,13 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
                 const HostPass &p = ex[t].planp->passes[k];
                 const bool with_epi = ex[t].epi && k + 1 == ex[t].planp->passes.size();
                 const bool lds = p.norm_out || p.dev_phases.size() > 1 || with_epi;
-                // a first pass that reads a boundary snapshot keeps the
-                // default load policy (other tasks read the same snapshot)
-                const bool stream = ctx->stream_loads && !(k == 0 && ex[t].src);
+                const bool own = k == 0 && ex[t].src, stream = ctx->stream_loads && !own;
+                // a persistent launch keeps one policy for all its passes
+                const IoPolicy io = persist ? (stream ? kIoStream : kIoShared)
+                                            : io_policy((int)n, m, p, fits, own, ctx->stream_loads);
                 if (p.jit_key.empty()) p.jit_key = jit_pass_key((int)n, m, p, p.norm_out || p.dev_phases.size() > 1);
                 const std::string key = (with_epi ? jit_pass_key((int)n, m, p, true) + *ex[t].epi_key : p.jit_key) +
-                                        (stream ? "S" : "T");
+                                        (char)io;
                 auto it = gi.find(key);
                 if (it == gi.end()) {
                     it = gi.emplace(key, members[k].size()).first;
@@ -944,7 +953,7 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
                     r.n = (int)n;
                     r.m = m;
                     r.use_lds = lds;
-                    r.stream_loads = stream;
+                    r.io = io;
                     reqs.push_back(std::move(r));
                 }
                 members[k][it->second].second.push_back(t);
@@ -1051,7 +1060,7 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
                 q.epi_key = ex[order[k][g.first]].epi_key;
                 q.n = (int)n;
                 q.m = m;
-                q.stream_loads = reqs[g.req].stream_loads;
+                q.stream_loads = reqs[g.req].io == kIoStream;
                 parts.push_back(q);
             }
         JitReq pr;
@@ -2630,6 +2639,23 @@ int qw_plan_cost(uint32_t n, const qw_gate *gates, uint64_t n_gates, uint32_t ti
     return QW_OK;
 }
 
+}  // extern "C"
+namespace {
+// The cache policies that calls can ask of a pass: with few states or many
+// and under either setting of QW_OPT_STREAM_LOADS, the first one also from a
+// separate source.
+std::set<IoPolicy> io_policies(int n, int m, const HostPass &p, bool first) {
+    std::set<IoPolicy> s;
+    for (int v = 0; v < 8; ++v) {
+        const bool fits = v & 1, own = v & 2, stream = v & 4;
+        if ((fits && (8ull << n) > kIoCacheBytes) || (own && !first)) continue;
+        s.insert(io_policy(n, m, p, fits, own, stream));
+    }
+    return s;
+}
+}  // namespace
+extern "C" {
+
 int qw_jit_precompile(uint32_t n, const qw_gate *gates, uint64_t n_gates, uint32_t tile_bits,
                       char *log, uint64_t cap) {
     auto put = [&](const std::string &msg) {
@@ -2657,16 +2683,15 @@ int qw_jit_precompile(uint32_t n, const qw_gate *gates, uint64_t n_gates, uint32
     for (const Plan &p : pv)
         for (size_t k = 0; k < p.passes.size(); ++k) {
             const HostPass &h = p.passes[k];
-            // both load policies (QW_OPT_STREAM_LOADS, snapshot-reading first passes)
-            for (int stream = 1; stream >= 0; --stream) {
+            for (const IoPolicy io : io_policies((int)n, p.m, h, k == 0)) {
                 JitReq r;
                 r.use_lds = h.norm_out || h.dev_phases.size() > 1;
-                r.key = jit_pass_key((int)n, p.m, h, r.use_lds) + (stream ? "S" : "T");
+                r.key = jit_pass_key((int)n, p.m, h, r.use_lds) + (char)io;
                 if (!seen.insert(r.key).second) continue;
                 r.pass = &h;
                 r.n = (int)n;
                 r.m = p.m;
-                r.stream_loads = stream != 0;
+                r.io = io;
                 reqs.push_back(std::move(r));
             }
         }
@@ -2767,18 +2792,17 @@ int qw_jit_precompile_suffix(uint32_t n, const qw_gate *gates, uint64_t n_gates,
         for (size_t k = 0; k < pp.passes.size(); ++k) {
             const HostPass &h = pp.passes[k];
             const bool with_epi = fe.active && k + 1 == pp.passes.size();
-            // both load policies (QW_OPT_STREAM_LOADS, snapshot-reading first passes)
-            for (int stream = 0; stream <= 1; ++stream) {
+            for (const IoPolicy io : io_policies((int)n, pp.m, h, k == 0)) {
                 JitReq r;
                 r.use_lds = h.norm_out || h.dev_phases.size() > 1 || with_epi;
                 r.key = jit_pass_key((int)n, pp.m, h, r.use_lds) + (with_epi ? fe.key : std::string()) +
-                        (stream ? "S" : "T");
+                        (char)io;
                 if (!seen.insert(r.key).second) continue;
                 r.pass = &h;
                 r.epi = with_epi ? &fe.rplan : nullptr;
                 r.n = (int)n;
                 r.m = pp.m;
-                r.stream_loads = stream != 0;
+                r.io = io;
                 reqs.push_back(std::move(r));
             }
         }

@@ -196,10 +196,9 @@ __device__ __forceinline__ double lane_xor_d(double x) {
 // byte offset, so all accesses of a thread share one address register.
 // Word 3 is the raw (untyped) setting of CDNA buffer resources.
 // Cache policy of the global loads and stores (the buffer instructions'
-// auxiliary operand; 2 = non-temporal). A generated kernel defines them
-// before including this header: streamed state traffic that no other
-// wave reads again is marked non-temporal so it does not displace data that
-// is reused (a boundary snapshot read by many tasks). 0 = default policy.
+// auxiliary operand): 0 = default, 2 = non-temporal, 16 = device scope (a
+// store goes through the L2 instead of staying in it until the launch ends).
+// A generated kernel defines them before including this header.
 #ifndef QW_LD_AUX
 #define QW_LD_AUX 0
 #endif

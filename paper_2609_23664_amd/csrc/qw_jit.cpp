@@ -728,16 +728,61 @@ static size_t emit_pass_defs(Gen &g, int n, int m, const HostPass &p, bool use_l
     return hs.op.size();
 }
 
+// Amplitudes in one contiguous run of a tile, as a power of two: the lowest
+// index bits of the state that the pass loads (stores) which are tile bits.
+static int tile_run(int n, const HostPass &p, bool out) {
+    const std::vector<uint8_t> &pos = out ? p.out_pos : p.in_pos;
+    uint64_t set = 0;
+    for (int q = 0; q < n; ++q) {
+        if (!((p.local_mask >> q) & 1ull)) continue;
+        const uint64_t im = out && !p.out_img.empty() ? p.out_img[q] : 1ull << q;
+        if (im & (im - 1)) continue;  // the image of a control spans bits
+        const int b = __builtin_ctzll(im);
+        set |= 1ull << (pos.empty() ? b : pos[b]);
+    }
+    return __builtin_ctzll(~set);
+}
+
+// Every line below is a measurement of the same kernel under each policy
+// (us a launch, non-temporal both ways first; the results do not depend on it).
+IoPolicy io_policy(int n, int m, const HostPass &p, bool fits, bool own_source, bool stream_loads) {
+    // Resident states: the next pass finds them in the last-level cache, which
+    // non-temporal stores go past; plain stores leave the L2s full of dirty
+    // lines whose write-back the end of the launch waits for (a 20-qubit
+    // circuit 72.2, plain 73.3, written through 69.0; the second pass over four
+    // 22-qubit states 66.5 / 47.0; the relabelling pass of one 24-qubit state
+    // 72 / 50).
+    if (fits) return kIoThrough;
+    // A snapshot that the tasks of a batch share stays in the caches, the
+    // states written from it go past them (64 24-qubit states: 4,100 to 4,400,
+    // 4,800 with plain, 4,900 with written-through stores).
+    if (own_source) return kIoShared;
+    const int in = tile_run(n, p, false), out = tile_run(n, p, true);
+    // Whole tiles in and out: 1,780 / 1,550 at 29 qubits, 897 / 786 at 28.
+    if (in == m && out == m) return kIoThrough;
+    // Short store runs: one at a time they reach the memory as scattered
+    // writes; the L2 collects the neighbouring tiles' (in place with 128-byte
+    // runs 1,295 / 1,100 at 28 qubits, whole tiles to such runs 4,000 / 3,620
+    // for 64 24-qubit states). It gains down from runs of 1 KiB and loses 4 %
+    // from 2 KiB on.
+    if (out <= 7) return kIoCached;
+    // Otherwise: with long runs on both sides the other policies lose 5 to 7 %
+    // (747 / 796); short load runs gathered into whole tiles gain up to 5 %
+    // written through, which the next pass over the states loses again.
+    return stream_loads ? kIoStream : kIoShared;
+}
+
 std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int prefetch,
-                            const RedPlan *epi, bool stream_loads) {
+                            const RedPlan *epi, IoPolicy io) {
     Gen g;
     const int T = 1 << (m - 4);
     const int WG = T < 256 ? T : 256;
     g << "// generated pass kernel: " << n << " qubits, tile bits " << m << ", " << p.dev_ops.size()
       << " op records, " << p.dev_phases.size() << " phases, "
       << (use_lds ? "persistent LDS form" : "flat form") << "\n";
-    g << "#define QW_ST_AUX 2\n";
-    if (stream_loads) g << "#define QW_LD_AUX 2\n";
+    if (io == kIoStream || io == kIoShared) g << "#define QW_ST_AUX 2\n";
+    if (io == kIoThrough) g << "#define QW_ST_AUX 16\n";
+    if (io == kIoStream) g << "#define QW_LD_AUX 2\n";
     g << "#include \"qw_dev.h\"\nusing namespace qw;\n";
     g << "constexpr int M = " << m << ", T = " << T << ", WG = " << WG << ", PARTS = T / WG;\n";
     const bool remap = p.moves();
@@ -1500,7 +1545,7 @@ namespace {
 // Kernel source of a request with `prefetch` registers of the next tile.
 std::string req_source(const JitReq &r, int prefetch) {
     if (r.persist) return jit_persist_source(*r.persist, prefetch);
-    if (r.pass) return jit_pass_source(r.n, r.m, *r.pass, r.use_lds, prefetch, r.epi, r.stream_loads);
+    if (r.pass) return jit_pass_source(r.n, r.m, *r.pass, r.use_lds, prefetch, r.epi, r.io);
     return jit_reduce_source(r.n, r.m, *r.group, *r.rplan);
 }
 const char *req_kernel_name(const JitReq &r) {

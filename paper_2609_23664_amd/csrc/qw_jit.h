@@ -24,13 +24,28 @@ namespace qw {
 // key run the same generated kernel.
 std::string jit_pass_key(int n, int m, const HostPass &p, bool use_lds);
 
+// Cache policy of a generated pass's state loads and stores (the letter that
+// ends its key).
+enum IoPolicy : char {
+    kIoStream = 'S',  // both non-temporal
+    kIoShared = 'T',  // default loads, non-temporal stores
+    kIoCached = 'C',  // both default
+    kIoThrough = 'W'  // default loads, stores written through the L2
+};
+
+// States of a call that fit the last-level cache of the device (256 MB).
+constexpr uint64_t kIoCacheBytes = 256ull << 20;
+
+// The policy of pass p. `fits`: the states the call sweeps fit the last-level
+// cache; `own_source`: the pass reads another state than the one the call
+// writes (a boundary snapshot); `stream_loads`: QW_OPT_STREAM_LOADS.
+IoPolicy io_policy(int n, int m, const HostPass &p, bool fits, bool own_source, bool stream_loads);
+
 // Full HIP source of the generated kernel for a key's pass; `prefetch`
 // (0..16, even) is the number of registers of the next tile the persistent
 // form loads while working on the current one.
-// `stream_loads`: the pass's state loads are non-temporal (its stores always
-// are); false for a pass that reads a boundary snapshot other tasks share.
 std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int prefetch = 16,
-                            const RedPlan *epi = nullptr, bool stream_loads = true);
+                            const RedPlan *epi = nullptr, IoPolicy io = kIoStream);
 
 // Key suffix of a pass kernel with a fused expectation epilogue.
 std::string jit_epilogue_key(int n, int m, const HostPass &p, const RedPlan &epi);
@@ -78,7 +93,7 @@ struct JitReq {
     const RedPlan *epi = nullptr;  // pass kernels: fused expectation epilogue (persistent form)
     int n = 0, m = 0;
     bool use_lds = false;  // pass kernels: persistent LDS form
-    bool stream_loads = true;  // pass kernels: non-temporal state loads
+    IoPolicy io = kIoStream;  // pass kernels
 };
 
 // Launch a generated reducer over n_descs descriptors of its term group.
