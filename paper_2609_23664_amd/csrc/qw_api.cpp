@@ -675,6 +675,7 @@ struct Exec {
     const std::string *epi_key = nullptr;
     double *epi_part = nullptr;  // this task's [rows][epi_nt] partials
     uint32_t epi_nt = 0;
+    bool epi_by_tile = false;    // epi_part is its RowSum::acc
     // qw_run_tree: index (in the same execution) of the task whose final
     // state `src` is, or -1; such a task runs in a persistent launch
     int parent = -1;
@@ -1247,7 +1248,8 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
                     tile_major = !shared_src && (ctx->tile_order == 2 || (ctx->tile_order == 1 && relabel));
                 }
                 hipError_t er = g.k ? jit_launch(str, *g.k, dd + g.first, g.count, tiles,
-                                                 ctx->xcd_remap ? 1 : 0, ctx->n_cu, tile_major)
+                                                 ctx->xcd_remap ? 1 : 0, ctx->n_cu, tile_major,
+                                                 ex[order[k][g.first]].epi_by_tile && reqs[g.req].epi)
                                     : launch_pass(str, dd + g.first, g.count, n, (uint32_t)m,
                                                   ctx->xcd_remap ? 1 : 0, g.lds);
                 if (er != hipSuccess) return hip_fail(ctx, er, "pass launch");
@@ -1284,9 +1286,48 @@ void conj_cnot(uint64_t *x, uint64_t *z, int *neg, int c, int t) {
 struct FusedEpi {
     bool active = false;
     std::vector<char> fused;  // per term: reduced in the last pass
+    bool by_tile = false;     // leaves its values per tile (RedScratch)
     RedPlan rplan;
     std::string key;
 };
+
+// Scratch of an expectation over ns slots: the rows' partials, the results
+// and, when rows are swept tile by tile, every thread's values per tile
+// (fused terms first, then one term group after the other).
+struct RedScratch {
+    size_t part_bytes, out, acc, size;
+    RedScratch(uint32_t ns, uint32_t tiles, int m, uint32_t n_terms, bool by_tile) {
+        part_bytes = (size_t)ns * (tiles / red_row_tiles(tiles)) * n_terms * sizeof(double);
+        out = (part_bytes + 255) & ~size_t(255);
+        acc = (out + ns * sizeof(double) + 255) & ~size_t(255);
+        size = acc + (by_tile ? ((size_t)ns * tiles * n_terms << (m - 4)) * sizeof(float) : 0);
+    }
+};
+
+// Rows of kRedRowTiles tiles leave most of the CUs idle when a call has few
+// of them. With one tile a CU or less the tiles are swept on their own and
+// added afterwards: 50 terms of a 20-qubit state 111 -> 69 us (whole call), of
+// one with 22 qubits (256 tiles) 126 -> 92, 10 terms there 59 -> 47; the last
+// pass of 6 17-qubit tasks 38.8 -> 13.9. With two tiles a CU the added launch
+// loses it again (10 terms of 8 20-qubit states 63 -> 70).
+bool rows_by_tile(const qw_ctx *ctx, uint32_t ns, uint32_t tiles, int m, uint32_t n_terms) {
+    return tiles >= kRedRowTiles && (uint64_t)ns * tiles <= ctx->n_cu &&
+           RedScratch(ns, tiles, m, n_terms, true).size <= (64ull << 20);
+}
+
+// The scratch of an expectation; without room for the values per tile, rows
+// are swept whole.
+int ensure_reduce(qw_ctx *ctx, uint32_t ns, uint32_t tiles, int m, uint32_t n_terms, bool *by_tile) {
+    if (*by_tile) {
+        const std::string err = ctx->err;
+        if (ensure(ctx, ctx->scratch, RedScratch(ns, tiles, m, n_terms, true).size, "reduce scratch") == QW_OK)
+            return QW_OK;
+        (void)hipGetLastError();
+        ctx->err = err;
+        *by_tile = false;
+    }
+    return ensure(ctx, ctx->scratch, RedScratch(ns, tiles, m, n_terms, false).size, "reduce scratch");
+}
 
 void plan_fused_last(int n, int m, const HostPass &lp, const uint64_t *x, const uint64_t *z,
                      uint32_t n_terms, FusedEpi *fe);
@@ -1355,7 +1396,7 @@ void plan_fused_last(int n, int m, const HostPass &lp, const uint64_t *x, const 
 // Expectations for a list of slot pointers of one n-qubit layout.
 int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots,
                  const uint64_t *x, const uint64_t *z, const double *c, uint32_t n_terms,
-                 double *out, int out_is_host, const std::vector<char> *fused = nullptr) {
+                 double *out, int out_is_host, const FusedEpi *fe = nullptr) {
     const uint32_t ns = (uint32_t)slots.size();
     if (ns == 0) return QW_OK;
     const uint64_t full = (1ull << n) - 1;
@@ -1381,11 +1422,11 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
     const uint32_t rows = tiles / red_row_tiles(tiles);   // partial rows per slot
     // terms whose partials a fused pass epilogue already wrote are left out
     std::vector<TermGroup> groups;
-    if (fused && !small) {
+    if (fe && !small) {
         std::vector<uint32_t> idx;
         std::vector<uint64_t> xs;
         for (uint32_t j = 0; j < n_terms; ++j)
-            if (!(*fused)[j]) {
+            if (!fe->fused[j]) {
                 idx.push_back(j);
                 xs.push_back(x[j]);
             }
@@ -1424,6 +1465,19 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
             use_jit = jit_available(ctx->device, r);
         }
     }
+    // (a fused epilogue has already written in one of the two ways)
+    bool by_tile = fe ? fe->by_tile : use_jit && rows_by_tile(ctx, ns, tiles, m, n_terms);
+    if (!fe || !by_tile) {
+        int rc0 = ensure_reduce(ctx, ns, tiles, m, n_terms, &by_tile);
+        if (rc0) return rc0;
+    }
+    // sources of the rows' partials that are left to add up
+    const bool red_by_tile = by_tile && use_jit;
+    std::vector<RowSum> sums;
+    uint32_t n_chunks = 0;
+    size_t fcols_off = 0;
+    if (by_tile && fe) fcols_off = L.take(fe->rplan.cols.size() * sizeof(uint32_t));
+    const size_t sums_off = by_tile ? L.take((groups.size() + 1) * sizeof(RowSum)) : 0;
     std::vector<size_t> tb_off(groups.size(), 0);
     if (use_jit)
         for (size_t g = 0; g < groups.size(); ++g) tb_off[g] = L.take((size_t)tiles * sizeof(uint32_t));
@@ -1432,10 +1486,8 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
     const size_t desc_off = L.take(n_desc * (small ? sizeof(ReduceDescSmall) : sizeof(ReduceDesc)));
     int rc = ensure(ctx, ctx->plan, L.size, "plan buffer");
     if (rc) return rc;
-    const size_t part_bytes = (size_t)ns * rows * n_terms * sizeof(double);
     const size_t out_bytes = ns * sizeof(double);
-    rc = ensure(ctx, ctx->scratch, part_bytes + out_bytes + 256, "reduce scratch");
-    if (rc) return rc;
+    const RedScratch lay(ns, tiles, m, n_terms, by_tile);
     uint8_t *dbase = static_cast<uint8_t *>(ctx->plan.p);
     double *part = static_cast<double *>(ctx->scratch.p);
     const bool direct = out_is_host && out_bytes <= kResultDirect;
@@ -1444,11 +1496,26 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
         if (rc) return rc;
     }
     double *dout = direct ? static_cast<double *>(ctx->result.p)
-                   : out_is_host ? reinterpret_cast<double *>(static_cast<uint8_t *>(ctx->scratch.p) +
-                                                              ((part_bytes + 255) & ~size_t(255)))
+                   : out_is_host ? reinterpret_cast<double *>(static_cast<uint8_t *>(ctx->scratch.p) + lay.out)
                                  : out;
+    float *const acc = reinterpret_cast<float *>(static_cast<uint8_t *>(ctx->scratch.p) + lay.acc);
     std::vector<uint8_t> blob(L.size, 0);
     std::memcpy(blob.data() + coeff_off, c, n_terms * sizeof(double));
+    size_t acc_at = 0;   // floats taken of the values per tile
+    std::vector<size_t> acc_off(groups.size(), 0);
+    auto add_sum = [&](const std::vector<uint32_t> &cols, size_t cols_off) {
+        const uint32_t nt = (uint32_t)cols.size();
+        std::memcpy(blob.data() + cols_off, cols.data(), nt * sizeof(uint32_t));
+        sums.push_back({acc + acc_at, reinterpret_cast<const uint32_t *>(dbase + cols_off), nt, n_chunks});
+        n_chunks += (nt + 7u) / 8u;
+        acc_at += (size_t)ns * tiles * nt << (m - 4);
+    };
+    if (by_tile && fe) add_sum(fe->rplan.cols, fcols_off);
+    for (size_t g = 0; red_by_tile && g < groups.size(); ++g) {
+        acc_off[g] = acc_at;
+        add_sum(rplans[g].cols, c_off[g]);
+    }
+    if (!sums.empty()) std::memcpy(blob.data() + sums_off, sums.data(), sums.size() * sizeof(RowSum));
     if (small) {
         for (uint32_t j = 0; j < n_terms; ++j) {
             TermSmall t{};
@@ -1488,7 +1555,9 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
                 d.terms = reinterpret_cast<const TermDev *>(dbase + t_off[g]);
                 d.phases = reinterpret_cast<const RedPhase *>(dbase + p_off[g]);
                 d.cols = reinterpret_cast<const uint32_t *>(dbase + c_off[g]);
-                d.part = part + (size_t)s * rows * n_terms;
+                d.part = red_by_tile ? reinterpret_cast<double *>(
+                                           acc + acc_off[g] + ((size_t)s * tiles * rplans[g].cols.size() << (m - 4)))
+                                     : part + (size_t)s * rows * n_terms;
                 d.local_mask = groups[g].local_mask;
                 d.n_phases = (uint32_t)rplans[g].phases.size();
                 d.n_terms = (uint32_t)rplans[g].terms.size();
@@ -1518,7 +1587,7 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
         ProfScope ps(ctx, 1, (double)ns * groups.size() * (double)(8ull << n), (uint32_t)groups.size());
         for (size_t g = 0; g < groups.size(); ++g) {
             hipError_t er = jit_launch_reduce(ctx->stream, *rk[g], dd + g * ns, ns, tiles, ctx->n_cu,
-                                              ctx->tile_order == 2);
+                                              ctx->tile_order == 2, red_by_tile);
             if (er != hipSuccess) return hip_fail(ctx, er, "generated reduce launch");
         }
     } else if (small || !groups.empty()) {
@@ -1529,6 +1598,11 @@ int expect_slots(qw_ctx *ctx, uint32_t n, const std::vector<const void *> &slots
             : launch_reduce(ctx->stream, reinterpret_cast<const ReduceDesc *>(dbase + desc_off),
                             (uint32_t)n_desc, n, (uint32_t)m);
         if (er != hipSuccess) return hip_fail(ctx, er, "reduce launch");
+    }
+    if (!sums.empty()) {
+        hipError_t es = launch_row_sum(ctx->stream, reinterpret_cast<const RowSum *>(dbase + sums_off),
+                                       (uint32_t)sums.size(), n_chunks, part, n_terms, tiles, ns, 1u << (m - 4));
+        if (es != hipSuccess) return hip_fail(ctx, es, "row sum launch");
     }
     hipError_t er = launch_expect_finalize(ctx->stream, part,
                                            reinterpret_cast<const double *>(dbase + coeff_off),
@@ -2270,14 +2344,19 @@ int qw_run_suffix_batch(qw_ctx *ctx, const qw_snap *const *src, const qw_task *t
         const int m = ex[0].planp->m;
         const uint32_t tiles = 1u << (dst->n - m);
         const uint32_t rows = tiles / red_row_tiles(tiles);
-        const size_t part_bytes = (size_t)n_tasks * rows * epi->n_terms * sizeof(double);
-        int rc0 = ensure(ctx, ctx->scratch, part_bytes + n_tasks * sizeof(double) + 256, "reduce scratch");
+        fe.by_tile = !ctx->persistent && rows_by_tile(ctx, n_tasks, tiles, m, epi->n_terms);
+        int rc0 = ensure_reduce(ctx, n_tasks, tiles, m, epi->n_terms, &fe.by_tile);
         if (rc0) return rc0;
         double *part = static_cast<double *>(ctx->scratch.p);
+        float *acc = reinterpret_cast<float *>(static_cast<uint8_t *>(ctx->scratch.p) +
+                                               RedScratch(n_tasks, tiles, m, epi->n_terms, true).acc);
+        const size_t per_task = (size_t)tiles * fe.rplan.cols.size() << (m - 4);
         for (uint32_t k = 0; k < n_tasks; ++k) {
             ex[k].epi = &fe.rplan;
             ex[k].epi_key = &fe.key;
-            ex[k].epi_part = part + (size_t)k * rows * epi->n_terms;
+            ex[k].epi_by_tile = fe.by_tile;
+            ex[k].epi_part = fe.by_tile ? reinterpret_cast<double *>(acc + k * per_task)
+                                        : part + (size_t)k * rows * epi->n_terms;
             ex[k].epi_nt = epi->n_terms;
         }
     }
@@ -2288,7 +2367,7 @@ int qw_run_suffix_batch(qw_ctx *ctx, const qw_snap *const *src, const qw_task *t
         std::vector<const void *> slots(n_tasks);
         for (uint32_t k = 0; k < n_tasks; ++k) slots[k] = slot_ptr(dst, tasks[k].dst_slot);
         return expect_slots(ctx, dst->n, slots, epi->x_mask, epi->z_mask, epi->coeff,
-                            epi->n_terms, epi->out, epi->out_is_host, fe.active ? &fe.fused : nullptr);
+                            epi->n_terms, epi->out, epi->out_is_host, fe.active ? &fe : nullptr);
     }
     return QW_OK;
 }

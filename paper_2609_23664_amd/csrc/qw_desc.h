@@ -149,7 +149,7 @@ struct alignas(16) PassDesc {
     const uint32_t *tile_base_out;  // PD_REMAP_OUT: L(tile_base), per tile
     const IoRec *io_in;    // address record of phase 0
     const IoRec *io_out;   // address record of the last phase
-    double *red_part;      // fused expectation epilogue: [rows][red_nt] FP64 partials
+    double *red_part;      // fused expectation epilogue: [rows][red_nt] FP64 partials (or RowSum::acc)
     uint32_t n_ops;
     uint32_t n_phases;
     uint32_t flags;
@@ -197,6 +197,17 @@ constexpr uint32_t kSyncClaim = 0, kSyncAbort = 1, kSyncCounters = 2;
 // workgroup processed it or on the launch's item order.
 constexpr uint32_t kRedRowTiles = 4;
 constexpr uint32_t red_row_tiles(uint32_t tiles) { return tiles < kRedRowTiles ? tiles : kRedRowTiles; }
+
+// A generated reducer (or fused epilogue) may instead sweep single tiles and
+// leave each thread's values for row_sum_kernel, which adds a row's tiles in
+// the same order: acc[tile][column][thread], `part` (`red_part`) pointing at
+// the slot's acc.
+struct alignas(16) RowSum {
+    const float *acc;        // [slot][tile][nt][thread]
+    const uint32_t *cols;    // column -> column of the partial array
+    uint32_t nt;
+    uint32_t chunk0;         // first of its ceil(nt / 8) chunks of 8 columns
+};
 
 // Expectation reducer, small states (n < 10): the whole state is one tile
 // staged in LDS; one descriptor per slot.
@@ -248,7 +259,7 @@ struct alignas(16) ReduceDesc {
     const TermDev *terms;
     const RedPhase *phases;
     const uint32_t *cols;  // group-local column -> column of the partial array
-    double *part;          // [rows][n_terms_total] of this slot (see kRedRowTiles)
+    double *part;          // [rows][n_terms_total] of this slot (see kRedRowTiles; or RowSum::acc)
     const uint32_t *tile_base;  // global index of local index 0, per tile
     uint64_t local_mask;
     uint32_t n_phases;

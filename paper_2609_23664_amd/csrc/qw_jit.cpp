@@ -816,9 +816,9 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
              "}\n";
     } else {
         g << "extern \"C\" __global__ __launch_bounds__(T) void qw_pass(const PassDesc *__restrict__ "
-             "descs, uint32_t n_descs, uint32_t items, int remap, uint32_t tmaj) {\n"
-             "    (void)remap;\n"
-             "    // item -> (descriptor, tile" << (epi ? " row" : "") << "): tmaj = 0 descriptor-fastest, else\n"
+             "descs, uint32_t n_descs, uint32_t items, int " << (epi ? "by_tile" : "remap") << ", uint32_t tmaj) {\n"
+          << (epi ? "    const uint32_t rt = by_tile ? 1u : RT;   // tiles of an item\n" : "    (void)remap;\n")
+          << "    // item -> (descriptor, tile" << (epi ? " row" : "") << "): tmaj = 0 descriptor-fastest, else\n"
              "    // tile-fastest with 1 << (tmaj - 1) items per descriptor\n"
              "    const uint32_t tg = tmaj ? tmaj - 1u : 0u;\n"
              "    auto desc_of = [=](uint32_t it) { return tmaj ? (it >> tg) : (it % n_descs); };\n"
@@ -870,7 +870,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
                  "    float acc[ENT];\n"
                  "    #pragma unroll\n"
                  "    for (int i = 0; i < ENT; ++i) acc[i] = 0.f;\n";
-        const char *tile0 = epi ? "tile_of(item) * RT" : "tile_of(item)";
+        const char *tile0 = epi ? "tile_of(item) * rt" : "tile_of(item)";
         g << "    float2 nv[" << std::max(1, PF) << "];\n"
              "    {\n"
              "        const PassDesc *d0 = descs + desc_of(item);\n"
@@ -880,7 +880,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
              "        float2 v[16];\n"
              "        #pragma unroll\n"
              "        for (int k = 0; k < " << PF << "; ++k) v[k] = nv[k];\n"
-             "        const uint32_t p = desc_of(item), tile = " << (epi ? "tile_of(item) * RT + rk" : "tile_of(item)")
+             "        const uint32_t p = desc_of(item), tile = " << (epi ? "tile_of(item) * rt + rk" : "tile_of(item)")
           << ";\n"
              "        const PassDesc *d = descs + p;\n"
              "        const uint64_t base = uni(ldu(ldu(&d->tile_base) + tile));\n"
@@ -894,7 +894,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
         if (epi)
             g << "        uint32_t next = item, nk = rk + 1u, nr = rr, nkk = kk;\n"
                  "        bool has_next = true;\n"
-                 "        if (nk == RT) {\n"
+                 "        if (nk == rt) {\n"
                  "            nk = 0u;\n"
                  "            has_next = advance(nr, nkk);\n"
                  "            next = first + j + wpx * nkk;\n"
@@ -906,7 +906,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
         g << "        if (has_next) {\n"
              "            const PassDesc *dn = descs + desc_of(next);\n"
              "            load_pre(nv, ldu(&dn->src), uni(ldu(ldu(&dn->tile_base) + "
-          << (epi ? "tile_of(next) * RT + nk" : "tile_of(next)") << ")) | wi, li);\n"
+          << (epi ? "tile_of(next) * rt + nk" : "tile_of(next)") << ")) | wi, li);\n"
              "        }\n";
         if (p.scale_in) g << kScaleIn;
         if (K)
@@ -930,7 +930,14 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
         g << "        store_out(v, ldu(&d->dst), ((uint64_t)" << obase << " ^ wx) | wo, lo);\n";
         if (epi)
             g << "        epi_tile(v, tid, lane, base, lb, acc);\n"
-                 "        if (rk == RT - 1u) {\n"
+                 "        if (by_tile) {\n"
+                 "            float *ac = reinterpret_cast<float *>(ldu(&d->red_part)) + (uint64_t)tile * (ENT * T) + tid;\n"
+                 "            #pragma unroll\n"
+                 "            for (int i = 0; i < ENT; ++i) {\n"
+                 "                gout<float>(ac)[i * T] = acc[i];\n"
+                 "                acc[i] = 0.f;\n"
+                 "            }\n"
+                 "        } else if (rk == RT - 1u) {\n"
                  "            epi_tile_flush(acc, lane, wave, red);\n"
                  "            __syncthreads();\n"
                  "            double *part = ldu(&d->red_part) + (uint64_t)tile_of(item) * ldu(&d->red_nt);\n"
@@ -1314,7 +1321,8 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
     // run in order on one workgroup, the next tile's load in flight
     o << "constexpr uint32_t RT = " << red_row_tiles(1u << (n - m)) << "u;\n";
     o << "extern \"C\" __global__ __launch_bounds__(T) void qw_reduce(const ReduceDesc *__restrict__ descs, "
-         "uint32_t n_descs, uint32_t items, uint32_t tmaj) {\n"
+         "uint32_t n_descs, uint32_t items, uint32_t tmaj, uint32_t by_tile) {\n"
+         "    const uint32_t rt = by_tile ? 1u : RT;   // tiles of an item\n"
          "    __shared__ float2 lds[1 << M];\n"
          "    __shared__ double red[W * NT];\n"
          "    const uint32_t tg = tmaj ? tmaj - 1u : 0u;\n"
@@ -1336,7 +1344,7 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
          "    float2 nv[16];\n"
          "    {\n"
          "        const ReduceDesc *d0 = descs + desc_of(item);\n"
-         "        load_in(nv, ldu(&d0->psi), uni(ldu(ldu(&d0->tile_base) + row_of(item) * RT)) | wi, li);\n"
+         "        load_in(nv, ldu(&d0->psi), uni(ldu(ldu(&d0->tile_base) + row_of(item) * rt)) | wi, li);\n"
          "    }\n"
          "    while (true) {\n"
          "        float2 v[16];\n"
@@ -1344,20 +1352,27 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
          "        for (int r = 0; r < 16; ++r) v[r] = nv[r];\n"
          "        const uint32_t p = desc_of(item), row = row_of(item);\n"
          "        const ReduceDesc *d = descs + p;\n"
-         "        const uint64_t base = uni(ldu(ldu(&d->tile_base) + row * RT + k));\n"
+         "        const uint64_t base = uni(ldu(ldu(&d->tile_base) + row * rt + k));\n"
          "        uint32_t ni = item, nk = k + 1u;\n"
-         "        if (nk == RT) {\n"
+         "        if (nk == rt) {\n"
          "            ni = item + wpx;\n"
          "            nk = 0u;\n"
          "        }\n"
          "        const bool has_next = ni < last;\n"
          "        if (has_next) {\n"
          "            const ReduceDesc *dn = descs + desc_of(ni);\n"
-         "            load_in(nv, ldu(&dn->psi), uni(ldu(ldu(&dn->tile_base) + row_of(ni) * RT + nk)) | wi, li);\n"
+         "            load_in(nv, ldu(&dn->psi), uni(ldu(ldu(&dn->tile_base) + row_of(ni) * rt + nk)) | wi, li);\n"
          "        }\n"
          "        __syncthreads();  // the previous tile's LDS and partial reads are done\n"
          "        tile(v, tid, lane, base, lb, acc);\n"
-         "        if (k == RT - 1u) {\n"
+         "        if (by_tile) {\n"
+         "            float *ac = reinterpret_cast<float *>(ldu(&d->part)) + (uint64_t)row * (NT * T) + tid;\n"
+         "            #pragma unroll\n"
+         "            for (int i = 0; i < NT; ++i) {\n"
+         "                gout<float>(ac)[i * T] = acc[i];\n"
+         "                acc[i] = 0.f;\n"
+         "            }\n"
+         "        } else if (k == RT - 1u) {\n"
          "            tile_flush(acc, lane, wave, red);\n"
          "            __syncthreads();\n"
          "            double *part = ldu(&d->part);\n"
@@ -1709,8 +1724,9 @@ static uint32_t tile_order_arg(uint32_t tiles, bool tile_major) {
 }
 
 hipError_t jit_launch(hipStream_t st, const JitKernel &k, const PassDesc *descs, uint32_t n_descs,
-                      uint32_t tiles, int remap, uint32_t cu_count, bool tile_major) {
-    const uint32_t rows = tiles / (uint32_t)k.row_tiles;
+                      uint32_t tiles, int remap, uint32_t cu_count, bool tile_major, bool by_tile) {
+    const uint32_t rows = by_tile ? tiles : tiles / (uint32_t)k.row_tiles;
+    if (k.row_tiles > 1) remap = by_tile;
     const uint32_t items = n_descs * rows;
     uint32_t tmaj = k.use_lds ? tile_order_arg(rows, tile_major) : 0u;
     uint32_t grid;
@@ -1729,8 +1745,10 @@ hipError_t jit_launch(hipStream_t st, const JitKernel &k, const PassDesc *descs,
 }
 
 hipError_t jit_launch_reduce(hipStream_t st, const JitKernel &k, const ReduceDesc *descs,
-                             uint32_t n_descs, uint32_t tiles, uint32_t cu_count, bool tile_major) {
-    const uint32_t rows = tiles / (uint32_t)k.row_tiles;
+                             uint32_t n_descs, uint32_t tiles, uint32_t cu_count, bool tile_major,
+                             bool by_tile) {
+    const uint32_t rows = by_tile ? tiles : tiles / (uint32_t)k.row_tiles;
+    uint32_t by_tile_arg = by_tile;
     uint32_t tmaj = tile_order_arg(rows, tile_major);
     const uint32_t items = n_descs * rows;
     const uint32_t full = cu_count * (uint32_t)k.blocks_per_cu;
@@ -1738,7 +1756,7 @@ hipError_t jit_launch_reduce(hipStream_t st, const JitKernel &k, const ReduceDes
     uint32_t grid = want < full ? want : (full / 8u) * 8u;
     if (grid < 8u) grid = 8u;
     uint32_t items_arg = items;
-    void *args[] = {&descs, &n_descs, &items_arg, &tmaj};
+    void *args[] = {&descs, &n_descs, &items_arg, &tmaj, &by_tile_arg};
     return hipModuleLaunchKernel(k.fn, grid, 1, 1, (uint32_t)k.wg, 1, 1, 0, st, args, nullptr);
 }
 

@@ -98,7 +98,8 @@ struct JitReq {
 
 // Launch a generated reducer over n_descs descriptors of its term group.
 hipError_t jit_launch_reduce(hipStream_t st, const JitKernel &k, const ReduceDesc *descs,
-                             uint32_t n_descs, uint32_t tiles, uint32_t cu_count, bool tile_major);
+                             uint32_t n_descs, uint32_t tiles, uint32_t cu_count, bool tile_major,
+                             bool by_tile);
 
 // Compiled kernels for the requests on `device`: loaded from memory, from
 // the disk cache, or compiled (in parallel). Returns "" or an error message.
@@ -115,8 +116,9 @@ std::string jit_precompile(const std::vector<JitReq> &reqs);
 // Launch a generated pass kernel over n_descs descriptors (all of its key).
 // `tile_major`: the persistent form takes consecutive tiles of one
 // descriptor (else the descriptors of one tile) as consecutive items.
+// `by_tile`: a kernel that takes rows of tiles takes single ones (see RowSum).
 hipError_t jit_launch(hipStream_t st, const JitKernel &k, const PassDesc *descs, uint32_t n_descs,
-                      uint32_t tiles, int remap, uint32_t cu_count, bool tile_major);
+                      uint32_t tiles, int remap, uint32_t cu_count, bool tile_major, bool by_tile);
 
 // Launch a persistent kernel over `claims` claims of n_segs segments on
 // `grid` workgroups (see PSeg, PDep; sync holds kSyncCounters + descriptor

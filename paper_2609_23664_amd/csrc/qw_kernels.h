@@ -35,6 +35,10 @@ hipError_t launch_reduce(hipStream_t st, const ReduceDesc *d, uint32_t n_descs, 
                          uint32_t M);
 hipError_t launch_reduce_small(hipStream_t st, const ReduceDescSmall *d, uint32_t n_descs,
                                uint32_t n);
+// Partials of rows swept tile by tile (see RowSum): part[slot][row][column]
+// from n_src sources with n_chunks chunks in all, T threads a tile.
+hipError_t launch_row_sum(hipStream_t st, const RowSum *src, uint32_t n_src, uint32_t n_chunks, double *part,
+                          uint32_t n_terms, uint32_t tiles, uint32_t n_slots, uint32_t T);
 // Per-slot sum over rows (see kRedRowTiles) and terms of the partials.
 hipError_t launch_expect_finalize(hipStream_t st, const double *part, const double *coeff,
                                   uint32_t n_terms, uint32_t rows, uint32_t n_slots,

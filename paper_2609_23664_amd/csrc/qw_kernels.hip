@@ -857,6 +857,46 @@ __global__ __launch_bounds__(1 << (M - 4)) void reduce_kernel(const ReduceDesc *
     }
 }
 
+// The rows' partials from each thread's values per tile (RowSum): one
+// workgroup per 8 columns of a row adds the row's tiles in FP32 in tile order,
+// then lanes and waves in FP64, as the reducers that sweep whole rows do.
+// Bound by latency: 32 loads a thread, all in flight, and two barriers.
+__global__ __launch_bounds__(1024) void row_sum_kernel(const RowSum *__restrict__ src, uint32_t n_src,
+                                                       double *__restrict__ part, uint32_t n_terms,
+                                                       uint32_t tiles) {
+    __shared__ double red[16 * 8];
+    const uint32_t chunk = blockIdx.x, row = blockIdx.y, slot = blockIdx.z, rows = gridDim.y;
+    const uint32_t T = blockDim.x, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    uint32_t s = 0;
+    while (s + 1u < n_src && src[s + 1u].chunk0 <= chunk) ++s;
+    const RowSum d = src[s];
+    const uint32_t j0 = 8u * (chunk - d.chunk0), rt = red_row_tiles(tiles);
+    const float *a = d.acc + ((uint64_t)slot * tiles + row * rt) * d.nt * T + tid;
+    float v[kRedRowTiles][8];
+    #pragma unroll
+    for (uint32_t k = 0; k < kRedRowTiles; ++k) {
+        #pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            v[k][i] = (k < rt && j0 + i < d.nt) ? a[((uint64_t)k * d.nt + j0 + i) * T] : 0.0f;
+    }
+    float q[8];
+    #pragma unroll
+    for (uint32_t i = 0; i < 8; ++i) {
+        q[i] = v[0][i];
+        #pragma unroll
+        for (uint32_t k = 1; k < kRedRowTiles; ++k) q[i] = k < rt ? q[i] + v[k][i] : q[i];
+    }
+    const double h = wave_reduce8(q, lane);
+    const uint32_t pos = 4u * (lane & 1u) + 2u * ((lane >> 1) & 1u) + ((lane >> 2) & 1u);
+    if (lane < 8u) red[wave * 8u + pos] = h;
+    __syncthreads();
+    if (tid < 8u && j0 + tid < d.nt) {
+        double sum = 0.0;
+        for (uint32_t w = 0; w < T / 64u; ++w) sum += red[w * 8u + tid];
+        part[((uint64_t)slot * rows + row) * n_terms + d.cols[j0 + tid]] = sum;
+    }
+}
+
 // out[s] = sum_j coeff[j] * (sum over rows of part[s][row][j]); one
 // workgroup per slot. A term's rows are added by one wave in the order of 256
 // threads taking rows t, t + 256, ... (four groups of 64 lanes, a butterfly
@@ -1543,6 +1583,16 @@ hipError_t launch_reduce_small(hipStream_t st, const ReduceDescSmall *d, uint32_
                                uint32_t n) {
     if (n_descs == 0) return hipSuccess;
     hipLaunchKernelGGL(reduce_small_kernel, dim3(n_descs), dim3(64 * kSmallWaves), 0, st, d, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_row_sum(hipStream_t st, const RowSum *src, uint32_t n_src, uint32_t n_chunks, double *part,
+                          uint32_t n_terms, uint32_t tiles, uint32_t n_slots, uint32_t T) {
+    const uint32_t rows = tiles / red_row_tiles(tiles);
+    if (n_chunks == 0 || n_slots == 0) return hipSuccess;
+    if (T < 64 || T > 1024 || n_slots > 65535 || rows > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(row_sum_kernel, dim3(n_chunks, rows, n_slots), dim3(T), 0, st, src, n_src, part,
+                       n_terms, tiles);
     return hipGetLastError();
 }
 
