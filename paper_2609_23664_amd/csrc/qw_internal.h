@@ -22,6 +22,9 @@ struct HostOp {
     std::vector<HostOp> members;  // OP_DSET: the OP_DIAG ops of the set
 };
 
+// States of a call that fit the last-level cache of the device (256 MB).
+constexpr uint64_t kIoCacheBytes = 256ull << 20;
+
 struct HostPass {
     uint64_t local_mask = 0;
     IoRec io_in{}, io_out{};      // filled by lower_pass() (register kernel)

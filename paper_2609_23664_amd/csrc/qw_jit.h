@@ -33,9 +33,6 @@ enum IoPolicy : char {
     kIoThrough = 'W'  // default loads, stores written through the L2
 };
 
-// States of a call that fit the last-level cache of the device (256 MB).
-constexpr uint64_t kIoCacheBytes = 256ull << 20;
-
 // The policy of pass p. `fits`: the states the call sweeps fit the last-level
 // cache; `own_source`: the pass reads another state than the one the call
 // writes (a boundary snapshot); `stream_loads`: QW_OPT_STREAM_LOADS.

@@ -672,11 +672,25 @@ __global__ __launch_bounds__(1024) void upload_kernel(uint4 *__restrict__ dst, c
 }
 
 // ------------------------------------------------------------- init / copy
-__global__ __launch_bounds__(256) void init_kernel(float4 *base, uint64_t slot_f4,
-                                                   uint64_t total_f4) {
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total_f4;
-         i += (uint64_t)gridDim.x * 256) {
-        base[i] = make_float4((i % slot_f4) == 0 ? 1.0f : 0.0f, 0.0f, 0.0f, 0.0f);
+// |0> into consecutive slots of slot_f4 (a power of two) float4. Bound by the
+// write rate: one float4 a thread and a 64-bit remainder for each took 5.4 us
+// for 8 MiB, 18.5 for 128 MiB and 339 for 2 GiB, this 4.6, 16.6 and 326.
+// THROUGH: written through the L2 (states that the next launch finds in the
+// last-level cache; no write-back at the end of the launch).
+constexpr uint32_t kInitPer = 4;   // float4 a thread writes at a time
+
+template <bool THROUGH>
+__global__ __launch_bounds__(256) void init_kernel(float4 *base, uint64_t slot_f4, uint64_t total_f4) {
+    const uint64_t step = (uint64_t)gridDim.x * (256 * kInitPer);
+    for (uint64_t c = (uint64_t)blockIdx.x * (256 * kInitPer); c < total_f4; c += step) {
+        #pragma unroll
+        for (uint32_t k = 0; k < kInitPer; ++k) {
+            const uint64_t i = c + k * 256 + threadIdx.x;
+            const qw_v4u q = {(i & (slot_f4 - 1)) == 0 ? __float_as_uint(1.0f) : 0u, 0u, 0u, 0u};
+            if (i < total_f4)
+                __builtin_amdgcn_raw_buffer_store_b128(q, rsrc_at(base, 2 * (c + k * 256)), threadIdx.x * 16u, 0,
+                                                       THROUGH ? 16 : 0);
+        }
     }
 }
 
@@ -1541,11 +1555,12 @@ hipError_t launch_init(hipStream_t st, void *base, uint32_t n, uint32_t n_slots)
         // n == 0 is rejected by the host; keep the kernel safe anyway
         return hipErrorInvalidValue;
     }
-    const uint64_t total = slot_f4 * n_slots;
-    uint64_t blocks = (total + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(init_kernel, dim3((uint32_t)blocks), dim3(256), 0, st,
-                       reinterpret_cast<float4 *>(base), slot_f4, total);
+    const uint64_t total = slot_f4 * n_slots, per = 256 * kInitPer;
+    const uint64_t blocks = std::min<uint64_t>((total + per - 1) / per, 65536);
+    if (blocks == 0) return hipSuccess;
+    auto *kernel = total * sizeof(float4) <= kIoCacheBytes ? init_kernel<true> : init_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(256), 0, st, reinterpret_cast<float4 *>(base),
+                       slot_f4, total);
     return hipGetLastError();
 }
 
