@@ -728,9 +728,9 @@ static size_t emit_pass_defs(Gen &g, int n, int m, const HostPass &p, bool use_l
     return hs.op.size();
 }
 
-// Amplitudes in one contiguous run of a tile, as a power of two: the lowest
-// index bits of the state that the pass loads (stores) which are tile bits.
-static int tile_run(int n, const HostPass &p, bool out) {
+// The index bits of the state that the pass loads (stores) which are tile
+// bits: a run of a tile is 2^k amplitudes for the lowest k bits set.
+static uint64_t tile_bits(int n, const HostPass &p, bool out) {
     const std::vector<uint8_t> &pos = out ? p.out_pos : p.in_pos;
     uint64_t set = 0;
     for (int q = 0; q < n; ++q) {
@@ -740,11 +740,12 @@ static int tile_run(int n, const HostPass &p, bool out) {
         const int b = __builtin_ctzll(im);
         set |= 1ull << (pos.empty() ? b : pos[b]);
     }
-    return __builtin_ctzll(~set);
+    return set;
 }
 
-// Every line below is a measurement of the same kernel under each policy
-// (us a launch, non-temporal both ways first; the results do not depend on it).
+// Every line below is a measurement of the same kernels under each policy (us
+// a launch or GB/s, non-temporal both ways first; the results do not depend
+// on it).
 IoPolicy io_policy(int n, int m, const HostPass &p, bool fits, bool own_source, bool stream_loads) {
     // Resident states: the next pass finds them in the last-level cache, which
     // non-temporal stores go past; plain stores leave the L2s full of dirty
@@ -757,15 +758,19 @@ IoPolicy io_policy(int n, int m, const HostPass &p, bool fits, bool own_source, 
     // states written from it go past them (64 24-qubit states: 4,100 to 4,400,
     // 4,800 with plain, 4,900 with written-through stores).
     if (own_source) return kIoShared;
-    const int in = tile_run(n, p, false), out = tile_run(n, p, true);
-    // Whole tiles in and out: 1,780 / 1,550 at 29 qubits, 897 / 786 at 28.
-    if (in == m && out == m) return kIoThrough;
-    // Short store runs: one at a time they reach the memory as scattered
-    // writes; the L2 collects the neighbouring tiles' (in place with 128-byte
-    // runs 1,295 / 1,100 at 28 qubits, whole tiles to such runs 4,000 / 3,620
-    // for 64 24-qubit states). It gains down from runs of 1 KiB and loses 4 %
-    // from 2 KiB on.
-    if (out <= 7) return kIoCached;
+    const uint64_t in = tile_bits(n, p, false), out = tile_bits(n, p, true), whole = (1ull << m) - 1;
+    const int run = __builtin_ctzll(~out);
+    // Whole tiles in and out, loaded 8 bytes a lane and worked on in several
+    // phases: 5 to 19 % faster at 22, 25 and 28 qubits (5 phases 4,770 / 5,677
+    // GB/s, 897 / 786 us at 28). With 16-byte loads 2 to 12 % slower (3 phases
+    // 5,824 / 5,246), and so is a single phase (5,662 / 5,384).
+    if (in == whole && out == whole && p.dev_phases.size() > 1 && p.io_in.kind == IO_F2) return kIoThrough;
+    // Short store runs at strides below 1 MiB: one at a time they reach the
+    // memory as scattered writes; the L2 collects the neighbouring tiles' (in
+    // place with 128-byte runs 1,295 / 1,100 us at 28 qubits, whole tiles to
+    // such runs 4,000 / 3,620 for 64 24-qubit states). Runs of 1 KiB and more
+    // gain nothing (0.95 to 1.06 of the rate), nor do larger strides.
+    if (run <= 6 && (out >> run) != 0 && run + __builtin_ctzll(out >> run) <= 16) return kIoCached;
     // Otherwise: with long runs on both sides the other policies lose 5 to 7 %
     // (747 / 796); short load runs gathered into whole tiles gain up to 5 %
     // written through, which the next pass over the states loses again.
