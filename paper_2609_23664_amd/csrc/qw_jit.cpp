@@ -1708,6 +1708,7 @@ std::string jit_get(int device, const std::vector<JitReq> &reqs, std::vector<con
         k->wg = use_lds ? T : (T < 256 ? T : 256);
         k->parts = use_lds ? 1 : T / k->wg;
         k->blocks_per_cu = 1;
+        k->epi = ks[i].pass && ks[i].epi;
         if ((!ks[i].pass && !ks[i].persist) || ks[i].epi) k->row_tiles = (int)red_row_tiles(1u << (ks[i].n - m));
         if (use_lds) {
             int nb = 0;
@@ -1731,7 +1732,7 @@ static uint32_t tile_order_arg(uint32_t tiles, bool tile_major) {
 hipError_t jit_launch(hipStream_t st, const JitKernel &k, const PassDesc *descs, uint32_t n_descs,
                       uint32_t tiles, int remap, uint32_t cu_count, bool tile_major, bool by_tile) {
     const uint32_t rows = by_tile ? tiles : tiles / (uint32_t)k.row_tiles;
-    if (k.row_tiles > 1) remap = by_tile;
+    remap = pass_mode_arg(k, remap, by_tile);
     const uint32_t items = n_descs * rows;
     uint32_t tmaj = k.use_lds ? tile_order_arg(rows, tile_major) : 0u;
     uint32_t grid;

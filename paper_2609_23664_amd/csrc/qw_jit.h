@@ -56,7 +56,15 @@ struct JitKernel {
     int blocks_per_cu = 1; // resident workgroups per CU (LDS form)
     int row_tiles = 1;     // reducers and pass kernels with an expectation
                            // epilogue: tiles per item (a row of kRedRowTiles)
+    bool epi = false;      // pass kernels: with an expectation epilogue
 };
+
+// The fourth argument of a pass kernel: with an expectation epilogue whether
+// it takes single tiles (and writes every thread's values, see RowSum), else
+// the XCD remap. Told by the kernel itself, not by its tiles per item: a state
+// of one tile has an epilogue with rows of one tile, and a remap taken for
+// by_tile would write past its partials.
+inline int pass_mode_arg(const JitKernel &k, int remap, bool by_tile) { return k.epi ? (by_tile ? 1 : 0) : remap; }
 
 // Exact structural key and source of the generated expectation reducer of
 // one term group (its terms, register phases and columns are fixed at
