@@ -1331,10 +1331,13 @@ struct RedScratch {
 // added afterwards: 50 terms of a 20-qubit state 111 -> 69 us (whole call), of
 // one with 22 qubits (256 tiles) 126 -> 92, 10 terms there 59 -> 47; the last
 // pass of 6 17-qubit tasks 38.8 -> 13.9. With two tiles a CU the added launch
-// loses it again (10 terms of 8 20-qubit states 63 -> 70).
+// loses it again (10 terms of 8 20-qubit states 63 -> 70). A context with a
+// memory cap does not grow its scratch for it: the bytes would be missing where
+// a state fitted (50 terms of one 22-qubit state take 52 MB, the state 34).
 bool rows_by_tile(const qw_ctx *ctx, uint32_t ns, uint32_t tiles, int m, uint32_t n_terms) {
+    const size_t size = RedScratch(ns, tiles, m, n_terms, true).size;
     return tiles >= kRedRowTiles && (uint64_t)ns * tiles <= ctx->n_cu &&
-           RedScratch(ns, tiles, m, n_terms, true).size <= (64ull << 20);
+           size <= (ctx->mem_cap ? ctx->scratch.cap : 64ull << 20);
 }
 
 // The scratch of an expectation; without room for the values per tile, rows
