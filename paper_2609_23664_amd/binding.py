@@ -253,7 +253,9 @@ def _f64_array(vals):
 
 def _prov(b: bytes):
     assert len(b) == 32
-    return (ctypes.c_uint8 * 32).from_buffer_copy(b)
+    if isinstance(b, (bytes, bytearray)):
+        return (ctypes.c_uint8 * 32).from_buffer_copy(b)
+    return (ctypes.c_uint8 * 32)(*b)   # any 32 numbers, one byte each
 
 
 def legality_check(kind: int, exactness: int, backend: int, n_qubits: int,
