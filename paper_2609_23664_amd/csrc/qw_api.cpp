@@ -354,7 +354,7 @@ uint32_t stage_pick(qw_ctx *ctx, size_t bytes) {
 // follows each copy: two passes over a 20-qubit state (12 KiB) 66.2 us a call
 // with it, 70.9 with a copy kernel, 69.2 with a copy and an event each. Above
 // 16 KiB it takes another route: 20 us per upload at 20 KiB, 23 at 256 KiB, 37
-// at 1 MiB, where a kernel that reads the pinned slot takes 3.5, 6 and 23 (25
+// at 1 MiB, where a kernel that reads the pinned slot takes 4.6, 8 and 23 (25
 // MiB: the same 470).
 constexpr uint32_t kTinySlot = 0xFFFFFFFFu;
 struct StagedBlob {

@@ -23,6 +23,10 @@ hipError_t launch_norm_finalize(hipStream_t st, const PassDesc *d, uint32_t n_de
 // by a kernel. *blocks workgroups (at most kUploadBlocks); workgroup b sets the
 // pinned word done[b] to `seq` when it has read its part of src.
 constexpr uint32_t kUploadBlocks = 64;
+constexpr uint32_t upload_blocks(uint64_t bytes) {
+    const uint64_t b = (bytes + 16383) / 16384;
+    return b < 1 ? 1u : b < kUploadBlocks ? (uint32_t)b : kUploadBlocks;
+}
 hipError_t launch_upload(hipStream_t st, void *dst, const void *src, uint64_t bytes, uint32_t *done,
                          uint32_t seq, uint32_t *blocks);
 // Every slot of [base, base + n_slots * 2^n) set to |0...0>.

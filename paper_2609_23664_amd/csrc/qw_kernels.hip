@@ -658,9 +658,11 @@ __global__ __launch_bounds__(256) void norm_finalize_kernel(const PassDesc *__re
 }
 
 // ------------------------------------------------------------- uploads
-// Plan data from pinned host memory: 16 KiB per workgroup (a 16-byte read over
-// the bus per thread, all in flight) up to 64 workgroups, then more rounds.
-// Bound by the bus: 1 MiB in 23 us, 8 KiB in 3.5 us. `done` tells the host that
+// Plan data from pinned host memory: at most 16 KiB per workgroup (a 16-byte
+// read over the bus per thread, all in flight) up to 64 workgroups, then more
+// rounds. Bound by the bus's latency, then its rate: 17 to 64 KiB in 4.7 us,
+// 240 KiB in 7.9 (8.4 with up to 32 KiB a workgroup), 1 MiB in 23. Smaller
+// blobs go another way (stage_blob). `done` tells the host that
 // the source has been read; the data itself is ordered by the kernel's end.
 __global__ __launch_bounds__(1024) void upload_kernel(uint4 *__restrict__ dst, const uint4 *__restrict__ src,
                                                       uint32_t count, uint32_t *done, uint32_t seq) {
@@ -1543,7 +1545,7 @@ hipError_t launch_upload(hipStream_t st, void *dst, const void *src, uint64_t by
                          uint32_t seq, uint32_t *blocks) {
     const uint64_t count = (bytes + 15) / 16;
     if (count > 0xFFFFFFFFull - 1024ull * kUploadBlocks) return hipErrorInvalidValue;
-    *blocks = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(count / 1024, 1), kUploadBlocks);
+    *blocks = upload_blocks(bytes);
     hipLaunchKernelGGL(upload_kernel, dim3(*blocks), dim3(1024), 0, st, static_cast<uint4 *>(dst),
                        static_cast<const uint4 *>(src), (uint32_t)count, done, seq);
     return hipGetLastError();
