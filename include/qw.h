@@ -219,7 +219,8 @@ int qw_ctx_sync(qw_ctx *ctx);
  *                         states exceed the last-level cache, except a first
  *                         pass that reads a boundary snapshot: other tasks
  *                         read it too); 0: default policy for every load.
- *                         Results do not depend on it [1]
+ *                         A kernel compiled for calls of fewer or more states
+ *                         may stand in. Results do not depend on it [1]
  *   QW_OPT_TILE_ORDER     order in which the persistent generated kernels
  *                         (multi-phase passes, reducers) take the
  *                         (task, tile) items of a launch: the tasks of one

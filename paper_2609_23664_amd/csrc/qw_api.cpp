@@ -155,6 +155,7 @@ struct qw_ctx {
     uint32_t persist_chunk = 8;      // QW_OPT_PERSIST_CHUNK: max tiles (rows) per claim
     std::vector<uint8_t> outcomes;  // outcome record of the last measured call
     std::unordered_map<std::string, uint64_t> jit_heat;  // task-tiles run per pass structure
+    std::unordered_map<std::string, uint64_t> stand_in;  // amplitudes run by stand-ins, per kernel asked for
     bool relabel = true;
     int layout = 1;              // QW_OPT_LAYOUT
     int tile_order = 1;          // QW_OPT_TILE_ORDER
@@ -686,6 +687,35 @@ std::string get_plan(qw_ctx *ctx, uint32_t n, const qw_gate *gates, uint64_t n_g
 // (same results).
 constexpr uint64_t kJitHotTiles = 4096;
 
+// The kernel of a pass structure for the other size class (few states or many:
+// another cache policy, the same results) stands in for one that would have to
+// be compiled, so that a call does not wait for a compiler where the number of
+// its states crosses the last-level cache. The right one is compiled once its
+// stand-in has run over this many amplitudes: policies differ by up to 19 % of
+// a pass, 5 % as a rule, which at 16 bytes an amplitude and 5 TB/s adds up to
+// 0.2 to 0.7 s by then; compiling a kernel takes 0.5 s. A recorded call takes
+// no stand-in where it may compile: a graph keeps its kernels.
+constexpr uint64_t kStandInAmps = 1ull << 40;
+
+// Whether a pass request runs without compiling. If its own kernel is not at
+// hand and the other class's is, the request becomes that one.
+bool ready_kernel(qw_ctx *ctx, JitReq &r, uint64_t amps, bool may_compile) {
+    auto it = ctx->stand_in.find(r.key);
+    // (a key with a stand-in was not on disk)
+    if (it == ctx->stand_in.end() ? jit_available(ctx->device, r) : jit_in_memory(ctx->device, r.key)) return true;
+    if (r.other_io == r.io || (may_compile && ctx->rec)) return false;
+    if (may_compile && it != ctx->stand_in.end() && it->second >= kStandInAmps) return false;
+    JitReq o = r;
+    o.io = r.other_io;
+    o.key.back() = (char)o.io;
+    // (the disk is asked where the alternative is a compile: it takes the source)
+    if (!jit_in_memory(ctx->device, o.key) && !(may_compile && jit_available(ctx->device, o))) return false;
+    if (ctx->stand_in.size() > 65536) ctx->stand_in.clear();
+    ctx->stand_in[r.key] += amps;
+    r = std::move(o);
+    return true;
+}
+
 // One task of an execution: its plan, source, destination.
 struct Exec {
     std::shared_ptr<const Plan> planp;
@@ -716,7 +746,19 @@ bool has_relabel(const Plan &p) {
 // a single state (qw_apply_prefix, measured segments) keep one launch per
 // pass, since a lone state has no other tasks to fill the device between
 // its dependent passes.
-int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch);
+int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch, bool fits);
+
+// Whether the states that a call reads and writes, with `second` second
+// buffers, fit the last-level cache (for the cache policies).
+bool states_fit(uint32_t n, const std::vector<Exec> &ex, uint64_t second) {
+    std::vector<const void *> swept;
+    for (const Exec &e : ex)
+        for (const void *s : {e.src, (const void *)e.dst})
+            if (s) swept.push_back(s);
+    std::sort(swept.begin(), swept.end());
+    swept.erase(std::unique(swept.begin(), swept.end()), swept.end());
+    return (swept.size() + second) * (8ull << n) <= kIoCacheBytes;
+}
 
 // Parallel branches of a recorded graph. The launches of one pass index, one
 // per pass structure, are independent: as a chain each of them ends in a wave
@@ -771,14 +813,15 @@ int execute(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch = false) 
     const uint64_t per = std::max<uint64_t>(1, ctx->pingpong_cap / state_bytes);
     uint64_t need = 0;
     for (const Exec &e : ex) need += has_relabel(*e.planp);
-    if (need <= per) return execute_chunk(ctx, n, ex, batch);
+    const bool fits = states_fit(n, ex, std::min(need, per));
+    if (need <= per) return execute_chunk(ctx, n, ex, batch, fits);
     std::vector<Exec> part;
     uint64_t cnt = 0;
     for (size_t i = 0; i < ex.size(); ++i) {
         part.push_back(ex[i]);
         cnt += has_relabel(*ex[i].planp);
         if (cnt == per || i + 1 == ex.size()) {
-            int rc = execute_chunk(ctx, n, part, batch);
+            int rc = execute_chunk(ctx, n, part, batch, fits);
             if (rc) return rc;
             part.clear();
             cnt = 0;
@@ -809,7 +852,7 @@ int assign_buffers(const Plan &p, bool external_src, std::vector<int> *db) {
     return 2;
 }
 
-int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
+int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch, bool fits) {
     if (ex.empty()) return QW_OK;
     const int m = ex[0].planp->m;
     const uint32_t tiles = (m >= kMinTileBits) ? (1u << (n - m)) : 1u;
@@ -993,14 +1036,6 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
     std::vector<std::vector<Group>> groups(steps);
     const bool use_jit = ctx->jit && m >= kMinTileBits;
     std::vector<JitReq> reqs;
-    // the states that the call reads and writes, for the cache policies
-    std::vector<const void *> swept;
-    for (size_t t = 0; t < ex.size(); ++t)
-        for (const void *s : {(const void *)ex[t].src, (const void *)ex[t].dst, (const void *)second[t]})
-            if (s) swept.push_back(s);
-    std::sort(swept.begin(), swept.end());
-    swept.erase(std::unique(swept.begin(), swept.end()), swept.end());
-    const bool fits = swept.size() * state_bytes <= kIoCacheBytes;
     if (use_jit) {
         std::vector<std::vector<std::pair<size_t, std::vector<size_t>>>> members(steps);
         for (size_t k = 0; k < steps; ++k) {
@@ -1029,42 +1064,45 @@ int execute_chunk(qw_ctx *ctx, uint32_t n, std::vector<Exec> &ex, bool batch) {
                     r.m = m;
                     r.use_lds = lds;
                     r.io = io;
+                    r.other_io = persist ? io : io_policy((int)n, m, p, !fits, own, ctx->stream_loads);
                     reqs.push_back(std::move(r));
                 }
                 members[k][it->second].second.push_back(t);
             }
         }
-        // tiered: generate a kernel when it is available without compiling,
-        // or when its structure has run enough work on this context to pay
-        // for compiling it
-        std::vector<char> want(reqs.size(), 1);
-        if (ctx->jit == 1 && !persist) {
+        // kernels not loaded yet. Tiered: one is generated when it is
+        // available without compiling, or when its structure has run enough
+        // work on this context to pay for compiling it
+        std::vector<const JitKernel *> kern(reqs.size(), nullptr);
+        if (!persist && !jit_loaded(ctx->device, reqs, &kern)) {
             std::vector<uint64_t> work(reqs.size(), 0);
             for (size_t k = 0; k < steps; ++k)
                 for (auto &gm : members[k]) work[gm.first] += (uint64_t)gm.second.size() * tiles;
+            std::vector<JitReq> sel;
+            std::vector<size_t> sel_of;
             for (size_t i = 0; i < reqs.size(); ++i) {
-                uint64_t &heat = ctx->jit_heat[reqs[i].key];
-                heat += work[i];
-                want[i] = reqs[i].epi || heat >= kJitHotTiles || jit_available(ctx->device, reqs[i]);
+                if (kern[i]) continue;
+                JitReq r = reqs[i];
+                bool hot = ctx->jit == 2 || r.epi;
+                if (ctx->jit == 1) {
+                    // (of the structure, whatever its policy)
+                    uint64_t &heat = ctx->jit_heat[r.key.substr(0, r.key.size() - 1)];
+                    heat += work[i];
+                    hot |= heat >= kJitHotTiles;
+                }
+                if (!ready_kernel(ctx, r, work[i] << m, hot) && !hot) continue;
+                sel_of.push_back(i);
+                sel.push_back(std::move(r));
             }
             if (ctx->jit_heat.size() > 65536) ctx->jit_heat.clear();
-        }
-        std::vector<JitReq> sel;
-        std::vector<size_t> sel_of(reqs.size(), (size_t)-1);
-        for (size_t i = 0; i < reqs.size(); ++i)
-            if (want[i]) {
-                sel_of[i] = sel.size();
-                sel.push_back(reqs[i]);
-            }
-        std::vector<const JitKernel *> kern(sel.size(), nullptr);
-        if (!persist) {
-            const std::string err = jit_get(ctx->device, sel, &kern);
+            std::vector<const JitKernel *> got;
+            const std::string err = jit_get(ctx->device, sel, &got);
             if (!err.empty()) return fail(ctx, QW_E_HIP, err);
+            for (size_t i = 0; i < sel.size(); ++i) kern[sel_of[i]] = got[i];
         }
         for (size_t k = 0; k < steps; ++k) {
             for (auto &gm : members[k]) {
-                const JitKernel *kk = sel_of[gm.first] == (size_t)-1 ? nullptr : kern[sel_of[gm.first]];
-                groups[k].push_back({kk, (uint32_t)order[k].size(), (uint32_t)gm.second.size(),
+                groups[k].push_back({kern[gm.first], (uint32_t)order[k].size(), (uint32_t)gm.second.size(),
                                      reqs[gm.first].use_lds, (uint32_t)gm.first});
                 for (size_t t : gm.second) order[k].push_back(t);
             }
@@ -2481,7 +2519,7 @@ int qw_run_tree(qw_ctx *ctx, const qw_snap *const *src, const qw_task *tasks, co
     }
     if (ctx->rec) ctx->rec->calls.emplace_back();
     if (one || !any_parent) {
-        if (one) return execute_chunk(ctx, dst->n, ex, true);
+        if (one) return execute_chunk(ctx, dst->n, ex, true, false);   // (persistent: one policy)
         return execute(ctx, dst->n, ex, true);
     }
     // level by level: a task runs in the execution after its parent's

@@ -1573,12 +1573,14 @@ const char *req_kernel_name(const JitReq &r) {
 }
 }  // namespace
 
-bool jit_available(int device, const JitReq &r) {
+bool jit_in_memory(int device, const std::string &key) {
     Registry &R = reg();
-    {
-        std::lock_guard<std::mutex> lk(R.mu);
-        if (R.kernels.count({device, r.key}) || R.code.count(r.key)) return true;
-    }
+    std::lock_guard<std::mutex> lk(R.mu);
+    return R.kernels.count({device, key}) || R.code.count(key);
+}
+
+bool jit_available(int device, const JitReq &r) {
+    if (jit_in_memory(device, r.key)) return true;
     const std::string dir = cache_dir();
     if (dir.empty()) return false;
     const std::string src = req_source(r, 16);
@@ -1660,24 +1662,23 @@ std::string jit_precompile(const std::vector<JitReq> &ks) {
     return "";
 }
 
+bool jit_loaded(int device, const std::vector<JitReq> &reqs, std::vector<const JitKernel *> *out) {
+    Registry &R = reg();
+    out->assign(reqs.size(), nullptr);
+    std::lock_guard<std::mutex> lk(R.mu);
+    bool all = true;
+    for (size_t i = 0; i < reqs.size(); ++i) {
+        auto it = R.kernels.find({device, reqs[i].key});
+        if (it == R.kernels.end()) all = false;
+        else (*out)[i] = it->second.get();
+    }
+    return all;
+}
+
 std::string jit_get(int device, const std::vector<JitReq> &reqs, std::vector<const JitKernel *> *out) {
     Registry &R = reg();
     const std::vector<JitReq> &ks = reqs;
-    out->assign(ks.size(), nullptr);
-    {
-        // fast path: every kernel already loaded on this device
-        std::lock_guard<std::mutex> lk(R.mu);
-        bool all = true;
-        for (size_t i = 0; i < ks.size(); ++i) {
-            auto it = R.kernels.find({device, ks[i].key});
-            if (it == R.kernels.end()) {
-                all = false;
-                continue;
-            }
-            (*out)[i] = it->second.get();
-        }
-        if (all) return "";
-    }
+    if (jit_loaded(device, ks, out)) return "";
     {
         std::vector<JitReq> miss;
         for (size_t i = 0; i < ks.size(); ++i)

@@ -99,6 +99,7 @@ struct JitReq {
     int n = 0, m = 0;
     bool use_lds = false;  // pass kernels: persistent LDS form
     IoPolicy io = kIoStream;  // pass kernels
+    IoPolicy other_io = kIoStream;  // the one a call of the other size class asks for
 };
 
 // Launch a generated reducer over n_descs descriptors of its term group.
@@ -109,6 +110,14 @@ hipError_t jit_launch_reduce(hipStream_t st, const JitKernel &k, const ReduceDes
 // Compiled kernels for the requests on `device`: loaded from memory, from
 // the disk cache, or compiled (in parallel). Returns "" or an error message.
 std::string jit_get(int device, const std::vector<JitReq> &reqs, std::vector<const JitKernel *> *out);
+
+// The kernels of the requests that are loaded on `device` (nullptr for the
+// others); true when all are.
+bool jit_loaded(int device, const std::vector<JitReq> &reqs, std::vector<const JitKernel *> *out);
+
+// True when the kernel of a key is loaded on `device` or its code object is in
+// memory.
+bool jit_in_memory(int device, const std::string &key);
 
 // True when the kernel of a request is loaded on `device` or its code
 // object is in the process or disk cache (no compilation).
