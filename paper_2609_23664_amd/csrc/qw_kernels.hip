@@ -1367,18 +1367,18 @@ __global__ __launch_bounds__(256) void sub_sum_small_kernel(const float2 *const 
     }
 }
 
-// 8 lanes per (slot, shot), 32 shots per workgroup. The target u * total is
-// located by an 8-way search over the chunk prefixes, a scan of the chunk's
-// (at most 16) sub-chunk sums and a scan of one sub-chunk's (at most 64)
-// amplitudes, the running sum continuing in FP64 from the chunk prefix, one
-// element after the other. Where rounding leaves the target past a level's
-// last element, that level's last element of non-zero mass is taken, so every
-// outcome has non-zero probability. Few shots are bound by the chain of
-// dependent loads, which 8 lanes shorten (one thread per shot waited for
-// log2(chunks) + up to 80 of them); many by the scans, so the amplitudes of
-// the 32 shots go through LDS and one lane per shot adds them. 1,024 shots of
-// a 24-qubit state: 21 us with one thread per shot, now 8.4 us; 65,536 shots
-// of 64 18-qubit states: 18 us, now 17 us.
+// Draws. The target u * total of a shot is located by a search over the chunk
+// prefixes, a scan of the chunk's (at most 16) sub-chunk sums and a scan of one
+// sub-chunk's (at most 64) amplitudes, the running sum continuing in FP64 from
+// the chunk prefix, one element after the other. Where rounding leaves the
+// target past a level's last element, that level's last element of non-zero
+// mass is taken, so every outcome has non-zero probability.
+//
+// Few shots: 8 lanes per shot, 32 shots per workgroup. They are bound by the
+// chain of dependent loads, which 8 lanes shorten (one thread per shot waited
+// for log2(chunks) + up to 80 of them); the amplitudes of the 32 shots go
+// through LDS and one lane per shot adds them. 1,024 shots of a 24-qubit state:
+// 21 us with one thread per shot, 8.4 us like this.
 constexpr uint32_t kDrawLanes = 8, kDrawShots = 256 / kDrawLanes;
 
 __global__ __launch_bounds__(256) void draw_kernel(const float2 *const *__restrict__ slots,
@@ -1396,99 +1396,186 @@ __global__ __launch_bounds__(256) void draw_kernel(const float2 *const *__restri
     const uint32_t lane = threadIdx.x & (kDrawLanes - 1), shot = threadIdx.x / kDrawLanes;
     const uint32_t group = (threadIdx.x & 63u) & ~(kDrawLanes - 1);
     const uint32_t spc = 1u << (C - S), L = 1u << S;
-    const uint64_t all = (uint64_t)n_slots * shots;
-    for (uint64_t first = (uint64_t)blockIdx.x * kDrawShots; first < all; first += (uint64_t)gridDim.x * kDrawShots) {
-        const uint64_t want = first + shot;
-        const uint64_t gid = want < all ? want : all - 1;   // idle groups repeat the last shot
-        uint32_t s, sh;
-        if (all <= 0xFFFFFFFFull) {   // a 32-bit division where it suffices
-            s = (uint32_t)gid / shots;
-            sh = (uint32_t)gid - s * shots;
+    const uint32_t all = n_slots * shots, first = blockIdx.x * kDrawShots;   // at most kDrawMany
+    const uint32_t gid = first + shot < all ? first + shot : all - 1;   // idle groups repeat the last shot
+    const uint32_t s = gid / shots, sh = gid - s * shots;
+    const uint64_t h = splitmix(seed ^ (((task_base + s) << 32) + sh));
+    const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
+    const double target = u * total[s];
+    const double *pre = cpre + (uint64_t)s * chunks;
+    const double *cs = csum + (uint64_t)s * chunks;
+    // last chunk with pre[c] <= target, then back over chunks without mass
+    uint32_t lo = 0, len = chunks;
+    while (len > 1u) {
+        const uint32_t stride = len >= kDrawLanes ? len / kDrawLanes : 1u;
+        const bool in = lane * stride < len && pre[lo + lane * stride] <= target;
+        const uint32_t hit = (uint32_t)(__ballot(in) >> group) & ((1u << kDrawLanes) - 1u);
+        lo += hit ? (31u - (uint32_t)__clz(hit)) * stride : 0u;
+        len = stride;
+    }
+    while (lo > 0 && cs[lo] == 0.0) --lo;
+    const double *sb = ssum + ((uint64_t)s * chunks + lo) * spc;
+    double run = pre[lo], run_last = run;
+    #pragma unroll
+    for (uint32_t i = 0; i < 16 / kDrawLanes; ++i)
+        if (i * kDrawLanes + lane < spc) sub[shot][i * kDrawLanes + lane] = sb[i * kDrawLanes + lane];
+    lds_wave_sync();
+    // j: the first element that takes the running sum past the target
+    // (counted without branches), else the last one of non-zero mass
+    uint32_t j = 0, last_j = 0;
+    double at = run;   // running sum before element j
+    bool past = false;
+    #pragma unroll 4
+    for (uint32_t k = 0; k < spc; ++k) {
+        const double v = sub[shot][k];
+        at = past ? at : run;
+        last_j = v > 0.0 ? k : last_j;
+        run_last = v > 0.0 ? run : run_last;
+        run += v;
+        past = past || run > target;
+        j += past ? 0u : 1u;
+    }
+    if (!past) {
+        j = last_j;
+        at = run_last;
+    }
+    const uint64_t base = ((uint64_t)lo << C) + ((uint64_t)j << S);
+    const float2 *psi = slots[s] + base;
+    #pragma unroll
+    for (uint32_t i = 0; i < 64 / kDrawLanes; ++i) {
+        const uint32_t l = i * kDrawLanes + lane;
+        if (l < L) {
+            const float2 a = psi[l];
+            const double x = a.x, y = a.y;
+            prob[shot][l] = fma(x, x, y * y);
+        }
+    }
+    if (lane == 0) {
+        s_at[shot] = at;
+        s_target[shot] = target;
+        s_base[shot] = (uint32_t)base;
+    }
+    __syncthreads();
+    const uint32_t q = threadIdx.x;
+    if (q < kDrawShots && first + q < all) {
+        const double tq = s_target[q];
+        double rq = s_at[q];
+        uint32_t res = 0, last_i = 0;
+        bool over = false;
+        auto step = [&](uint32_t i) {
+            const double pr = prob[q][i];
+            rq += pr;
+            last_i = pr > 0.0 ? i : last_i;
+            over = over || rq > tq;
+            res += over ? 0u : 1u;
+        };
+        if (L == 64u) {
+            #pragma unroll
+            for (uint32_t i = 0; i < 64u; ++i) step(i);
         } else {
-            s = (uint32_t)(gid / shots);
-            sh = (uint32_t)(gid % shots);
+            for (uint32_t i = 0; i < L; ++i) step(i);
         }
-        const uint64_t h = splitmix(seed ^ (((task_base + s) << 32) + sh));
-        const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
-        const double target = u * total[s];
-        const double *pre = cpre + (uint64_t)s * chunks;
-        const double *cs = csum + (uint64_t)s * chunks;
-        // last chunk with pre[c] <= target, then back over chunks without mass
-        uint32_t lo = 0, len = chunks;
-        while (len > 1u) {
-            const uint32_t stride = len >= kDrawLanes ? len / kDrawLanes : 1u;
-            const bool in = lane * stride < len && pre[lo + lane * stride] <= target;
-            const uint32_t hit = (uint32_t)(__ballot(in) >> group) & ((1u << kDrawLanes) - 1u);
-            lo += hit ? (31u - (uint32_t)__clz(hit)) * stride : 0u;
-            len = stride;
-        }
-        while (lo > 0 && cs[lo] == 0.0) --lo;
-        const double *sb = ssum + ((uint64_t)s * chunks + lo) * spc;
-        double run = pre[lo], run_last = run;
+        if (!over) res = last_i;
+        out[first + q] = s_base[q] + res;
+    }
+}
+
+// Many shots (more than kDrawMany): one thread per shot. They are bound by the
+// scans' additions; with 8 lanes a shot one of a workgroup's four waves adds,
+// and all 64 amplitudes of its 32 shots whatever the state. Here every thread
+// adds, and stops after the 4 sums and the 8 amplitudes (64 bytes, all loads in
+// flight) in which its target lies. Whole calls with 8 lanes a shot / like this
+// (with one thread a shot and a load for every element): 65,536 shots of 64
+// 18-qubit states, spread 721 / 331 us (688), GHZ 522 / 159 (222), |0...0>
+// 499 / 67 (67); 2^20 shots of a 26-qubit state 410 / 283 (633). The line:
+// 32,768 shots of an 18-qubit state 17.3 / 18.5, 65,536 22.3 / 18.9. Loads of 16
+// amplitudes gain 4 % on 18 to 26 spread qubits and lose 6 % on 14 (223 / 237).
+constexpr uint64_t kDrawMany = 49152;
+
+template <bool WIDE>
+__global__ __launch_bounds__(256) void draw_many_kernel(
+    const float2 *const *__restrict__ slots, uint32_t n_slots, uint32_t C, uint32_t S, uint32_t chunks,
+    const double *__restrict__ csum, const double *__restrict__ cpre, const double *__restrict__ ssum,
+    const double *__restrict__ total, uint64_t seed, uint64_t task_base, uint32_t shots,
+    uint32_t *__restrict__ out) {
+    const uint64_t gid = (uint64_t)blockIdx.x * 256 + threadIdx.x, all = (uint64_t)n_slots * shots;
+    if (gid >= all) return;
+    uint32_t s, sh;
+    if (all <= 0xFFFFFFFFull) {   // a 32-bit division where it suffices
+        s = (uint32_t)gid / shots;
+        sh = (uint32_t)gid - s * shots;
+    } else {
+        s = (uint32_t)(gid / shots);
+        sh = (uint32_t)(gid % shots);
+    }
+    const uint64_t h = splitmix(seed ^ (((task_base + s) << 32) + sh));
+    const double u = (double)(h >> 11) * (1.0 / 9007199254740992.0);
+    const double target = u * total[s];
+    const double *pre = cpre + (uint64_t)s * chunks;
+    const double *cs = csum + (uint64_t)s * chunks;
+    // last chunk with pre[c] <= target, then back over chunks without mass
+    uint32_t lo = 0;
+    for (uint32_t half = chunks >> 1; half > 0; half >>= 1)
+        if (pre[lo + half] <= target) lo += half;
+    while (lo > 0 && cs[lo] == 0.0) --lo;
+    const uint32_t spc = 1u << (C - S), L = 1u << S;
+    const double *sb = ssum + ((uint64_t)s * chunks + lo) * spc;
+    // j: the first element that takes the running sum past the target, else
+    // the last one of non-zero mass (the zeros after spc change neither)
+    double run = pre[lo], at = run, run_last = run;
+    uint32_t j = 0, last_j = 0;
+    bool past = false;
+    #pragma unroll
+    for (uint32_t k0 = 0; k0 < 16; k0 += 4) {
+        if (past) continue;
+        double v[4];
         #pragma unroll
-        for (uint32_t i = 0; i < 16 / kDrawLanes; ++i)
-            if (i * kDrawLanes + lane < spc) sub[shot][i * kDrawLanes + lane] = sb[i * kDrawLanes + lane];
-        lds_wave_sync();
-        // j: the first element that takes the running sum past the target
-        // (counted without branches), else the last one of non-zero mass
-        uint32_t j = 0, last_j = 0;
-        double at = run;   // running sum before element j
-        bool past = false;
-        #pragma unroll 4
-        for (uint32_t k = 0; k < spc; ++k) {
-            const double v = sub[shot][k];
+        for (uint32_t i = 0; i < 4; ++i) v[i] = k0 + i < spc ? sb[k0 + i] : 0.0;
+        #pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
             at = past ? at : run;
-            last_j = v > 0.0 ? k : last_j;
-            run_last = v > 0.0 ? run : run_last;
-            run += v;
+            last_j = v[i] > 0.0 ? k0 + i : last_j;
+            run_last = v[i] > 0.0 ? run : run_last;
+            run += v[i];
             past = past || run > target;
             j += past ? 0u : 1u;
         }
-        if (!past) {
-            j = last_j;
-            at = run_last;
-        }
-        const uint64_t base = ((uint64_t)lo << C) + ((uint64_t)j << S);
-        const float2 *psi = slots[s] + base;
-        #pragma unroll
-        for (uint32_t i = 0; i < 64 / kDrawLanes; ++i) {
-            const uint32_t l = i * kDrawLanes + lane;
-            if (l < L) {
-                const float2 a = psi[l];
-                const double x = a.x, y = a.y;
-                prob[shot][l] = fma(x, x, y * y);
-            }
-        }
-        if (lane == 0) {
-            s_at[shot] = at;
-            s_target[shot] = target;
-            s_base[shot] = (uint32_t)base;
-        }
-        __syncthreads();
-        const uint32_t q = threadIdx.x;
-        if (q < kDrawShots && first + q < all) {
-            const double tq = s_target[q];
-            double rq = s_at[q];
-            uint32_t res = 0, last_i = 0;
-            bool over = false;
-            auto step = [&](uint32_t i) {
-                const double pr = prob[q][i];
-                rq += pr;
-                last_i = pr > 0.0 ? i : last_i;
-                over = over || rq > tq;
-                res += over ? 0u : 1u;
-            };
-            if (L == 64u) {
-                #pragma unroll
-                for (uint32_t i = 0; i < 64u; ++i) step(i);
-            } else {
-                for (uint32_t i = 0; i < L; ++i) step(i);
-            }
-            if (!over) res = last_i;
-            out[first + q] = s_base[q] + res;
-        }
-        __syncthreads();   // the next shots reuse the LDS
     }
+    if (!past) {
+        j = last_j;
+        at = run_last;
+    }
+    const uint64_t base = ((uint64_t)lo << C) + ((uint64_t)j << S);
+    const float2 *psi = slots[s] + base;
+    uint32_t res = 0, last_i = 0;
+    bool over = false;
+    auto step = [&](uint32_t i, float re, float im) {
+        const double x = re, y = im, pr = fma(x, x, y * y);
+        at += pr;
+        last_i = pr > 0.0 ? i : last_i;
+        over = over || at > target;
+        res += over ? 0u : 1u;
+    };
+    if constexpr (WIDE) {
+        const float4 *p4 = reinterpret_cast<const float4 *>(psi);
+        #pragma unroll 1
+        for (uint32_t b = 0; b < 64u && !over; b += 8u) {
+            float4 q[4];
+            #pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) q[i] = p4[(b >> 1) + i];
+            #pragma unroll
+            for (uint32_t i = 0; i < 4; i += 2) {
+                if (over) continue;
+                step(b + 2 * i, q[i].x, q[i].y);
+                step(b + 2 * i + 1, q[i].z, q[i].w);
+                step(b + 2 * i + 2, q[i + 1].x, q[i + 1].y);
+                step(b + 2 * i + 3, q[i + 1].z, q[i + 1].w);
+            }
+        }
+    } else {
+        for (uint32_t i = 0; i < L && !over; ++i) step(i, psi[i].x, psi[i].y);
+    }
+    out[gid] = (uint32_t)base + (over ? res : last_i);
 }
 
 // ------------------------------------------------------------- launchers
@@ -1642,7 +1729,15 @@ hipError_t launch_sample(hipStream_t st, const float2 *const *slots, uint32_t n_
     if (e != hipSuccess) return e;
     const uint64_t draws = (uint64_t)n_slots * shots;
     if (draws == 0) return hipSuccess;
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>((draws + kDrawShots - 1) / kDrawShots, 1u << 20);
+    if (draws > kDrawMany) {
+        const uint64_t groups = (draws + 255) / 256;
+        if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
+        auto *kernel = S == 6 ? draw_many_kernel<true> : draw_many_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)groups), dim3(256), 0, st, slots, n_slots, C, S, chunks, csum,
+                           cpre, ssum, total, seed, task_base, shots, out);
+        return hipGetLastError();
+    }
+    const uint32_t blocks = (uint32_t)((draws + kDrawShots - 1) / kDrawShots);
     hipLaunchKernelGGL(draw_kernel, dim3(blocks), dim3(256), 0, st, slots, n_slots, C, S, chunks, csum, cpre,
                        ssum, total, seed, task_base, shots, out);
     return hipGetLastError();
