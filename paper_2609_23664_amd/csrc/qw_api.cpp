@@ -1374,7 +1374,7 @@ struct RedScratch {
 // a state fitted (50 terms of one 22-qubit state take 52 MB, the state 34).
 bool rows_by_tile(const qw_ctx *ctx, uint32_t ns, uint32_t tiles, int m, uint32_t n_terms) {
     const size_t size = RedScratch(ns, tiles, m, n_terms, true).size;
-    return tiles >= kRedRowTiles && (uint64_t)ns * tiles <= ctx->n_cu &&
+    return tiles >= kRedRowTiles && tiles <= kByTileMax && (uint64_t)ns * tiles <= ctx->n_cu &&
            size <= (ctx->mem_cap ? ctx->scratch.cap : 64ull << 20);
 }
 

@@ -777,6 +777,19 @@ IoPolicy io_policy(int n, int m, const HostPass &p, bool fits, bool own_source, 
     return stream_loads ? kIoStream : kIoShared;
 }
 
+// Rows and single tiles (see RowSum) in one kernel: item i covers the tiles
+// (i << rs) + k - k0, k = k0 .. RT - 1, and each ends its row at k == RT - 1. By
+// single tiles k starts there. With the tiles of an item a run-time value in the
+// place of RT the kernels ran out of registers: 35 terms on 20 qubits 128 and
+// 100 bytes of scratch, like this 127 and none (126 without single tiles); 50
+// terms of 128 20-qubit states 634 and 482 us.
+static std::string by_tile_defs(int n, int m) {
+    const uint32_t rt = red_row_tiles(1u << (n - m)), sh = (uint32_t)__builtin_ctz(rt);
+    if (!takes_by_tile(n, m))
+        return "    (void)by_tile;\n    constexpr uint32_t rs = " + std::to_string(sh) + "u, k0 = 0u;\n";
+    return "    const uint32_t rs = by_tile ? 0u : " + std::to_string(sh) + "u, k0 = by_tile ? RT - 1u : 0u;\n";
+}
+
 std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int prefetch,
                             const RedPlan *epi, IoPolicy io) {
     Gen g;
@@ -822,7 +835,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
     } else {
         g << "extern \"C\" __global__ __launch_bounds__(T) void qw_pass(const PassDesc *__restrict__ "
              "descs, uint32_t n_descs, uint32_t items, int " << (epi ? "by_tile" : "remap") << ", uint32_t tmaj) {\n"
-          << (epi ? "    const uint32_t rt = by_tile ? 1u : RT;   // tiles of an item\n" : "    (void)remap;\n")
+          << (epi ? by_tile_defs(n, m) : "    (void)remap;\n")
           << "    // item -> (descriptor, tile" << (epi ? " row" : "") << "): tmaj = 0 descriptor-fastest, else\n"
              "    // tile-fastest with 1 << (tmaj - 1) items per descriptor\n"
              "    const uint32_t tg = tmaj ? tmaj - 1u : 0u;\n"
@@ -871,11 +884,11 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
              "    uint32_t ft_desc = 0xFFFFFFFFu;   // descriptor they were computed for\n"
              "    (void)ft_desc;\n";
         if (epi)
-            g << "    uint32_t rk = 0;   // tile of the row\n"
+            g << "    uint32_t rk = k0;   // tile of the row\n"
                  "    float acc[ENT];\n"
                  "    #pragma unroll\n"
                  "    for (int i = 0; i < ENT; ++i) acc[i] = 0.f;\n";
-        const char *tile0 = epi ? "tile_of(item) * rt" : "tile_of(item)";
+        const char *tile0 = epi ? "(tile_of(item) << rs)" : "tile_of(item)";
         g << "    float2 nv[" << std::max(1, PF) << "];\n"
              "    {\n"
              "        const PassDesc *d0 = descs + desc_of(item);\n"
@@ -885,7 +898,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
              "        float2 v[16];\n"
              "        #pragma unroll\n"
              "        for (int k = 0; k < " << PF << "; ++k) v[k] = nv[k];\n"
-             "        const uint32_t p = desc_of(item), tile = " << (epi ? "tile_of(item) * rt + rk" : "tile_of(item)")
+             "        const uint32_t p = desc_of(item), tile = " << (epi ? "(tile_of(item) << rs) + (rk - k0)" : "tile_of(item)")
           << ";\n"
              "        const PassDesc *d = descs + p;\n"
              "        const uint64_t base = uni(ldu(ldu(&d->tile_base) + tile));\n"
@@ -899,8 +912,8 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
         if (epi)
             g << "        uint32_t next = item, nk = rk + 1u, nr = rr, nkk = kk;\n"
                  "        bool has_next = true;\n"
-                 "        if (nk == rt) {\n"
-                 "            nk = 0u;\n"
+                 "        if (nk == RT) {\n"
+                 "            nk = k0;\n"
                  "            has_next = advance(nr, nkk);\n"
                  "            next = first + j + wpx * nkk;\n"
                  "        }\n";
@@ -911,7 +924,7 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
         g << "        if (has_next) {\n"
              "            const PassDesc *dn = descs + desc_of(next);\n"
              "            load_pre(nv, ldu(&dn->src), uni(ldu(ldu(&dn->tile_base) + "
-          << (epi ? "tile_of(next) * rt + nk" : "tile_of(next)") << ")) | wi, li);\n"
+          << (epi ? "(tile_of(next) << rs) + (nk - k0)" : "tile_of(next)") << ")) | wi, li);\n"
              "        }\n";
         if (p.scale_in) g << kScaleIn;
         if (K)
@@ -935,21 +948,25 @@ std::string jit_pass_source(int n, int m, const HostPass &p, bool use_lds, int p
         g << "        store_out(v, ldu(&d->dst), ((uint64_t)" << obase << " ^ wx) | wo, lo);\n";
         if (epi)
             g << "        epi_tile(v, tid, lane, base, lb, acc);\n"
-                 "        if (by_tile) {\n"
-                 "            float *ac = reinterpret_cast<float *>(ldu(&d->red_part)) + (uint64_t)tile * (ENT * T) + tid;\n"
-                 "            #pragma unroll\n"
-                 "            for (int i = 0; i < ENT; ++i) {\n"
-                 "                gout<float>(ac)[i * T] = acc[i];\n"
-                 "                acc[i] = 0.f;\n"
-                 "            }\n"
-                 "        } else if (rk == RT - 1u) {\n"
-                 "            epi_tile_flush(acc, lane, wave, red);\n"
+                 "        if (rk == RT - 1u) {\n"
+              << (takes_by_tile(n, m)
+                      ? "            if (by_tile) {\n"
+                        "                float *ac = reinterpret_cast<float *>(ldu(&d->red_part)) + (uint64_t)tile * (ENT * T) + tid;\n"
+                        "                #pragma unroll\n"
+                        "                for (int i = 0; i < ENT; ++i) {\n"
+                        "                    gout<float>(ac)[i * T] = acc[i];\n"
+                        "                    acc[i] = 0.f;\n"
+                        "                }\n"
+                        "            } else {\n"
+                      : "            {\n")
+              << "            epi_tile_flush(acc, lane, wave, red);\n"
                  "            __syncthreads();\n"
                  "            double *part = ldu(&d->red_part) + (uint64_t)tile_of(item) * ldu(&d->red_nt);\n"
                  "            for (uint32_t c = tid; c < (uint32_t)ENT; c += T) {\n"
                  "                double s = 0.0;\n"
                  "                for (int ww = 0; ww < T / 64; ++ww) s += red[ww * ENT + c];\n"
                  "                gout<double>(part)[kECols[c]] = s;\n"
+                 "            }\n"
                  "            }\n"
                  "        }\n";
         g << "        if (!has_next) break;\n"
@@ -1324,11 +1341,23 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
     o << "};\n";
     // items are (descriptor, row of RT consecutive tiles); the row's tiles
     // run in order on one workgroup, the next tile's load in flight
-    o << "constexpr uint32_t RT = " << red_row_tiles(1u << (n - m)) << "u;\n";
+    // (one-tile states: with the end of a row a compile-time constant the sums'
+    // flush is run into the terms, 50 terms take 1,848 bytes of scratch and 256
+    // 14-qubit states 341 us; without 45, and 37 when the next tile is not loaded
+    // ahead, for which the registers are short. Smaller tiles gain too, several
+    // share a CU: 30 terms of 2,048 13-qubit states 98 and 81. One 14-bit tile of
+    // few terms a CU has nothing else to wait behind: 1 term of 4,096 states 113
+    // with the load ahead, 120 without)
+    const uint32_t rt = red_row_tiles(1u << (n - m));
+    const bool ahead = rt > 1u || (m == kMaxTileBits && NT <= 8);
+    o << "constexpr uint32_t RT = " << rt << "u;\n";
     o << "extern \"C\" __global__ __launch_bounds__(T) void qw_reduce(const ReduceDesc *__restrict__ descs, "
          "uint32_t n_descs, uint32_t items, uint32_t tmaj, uint32_t by_tile) {\n"
-         "    const uint32_t rt = by_tile ? 1u : RT;   // tiles of an item\n"
-         "    __shared__ float2 lds[1 << M];\n"
+      << by_tile_defs(n, m)
+      << (rt == 1u ? "    uint32_t end = 0u;   // the row's last tile (kept from the compiler)\n"
+                     "    asm(\"\" : \"+s\"(end));\n"
+                   : "    constexpr uint32_t end = RT - 1u;\n")
+      << "    __shared__ float2 lds[1 << M];\n"
          "    __shared__ double red[W * NT];\n"
          "    const uint32_t tg = tmaj ? tmaj - 1u : 0u;\n"
          "    auto desc_of = [=](uint32_t it) { return tmaj ? (it >> tg) : (it % n_descs); };\n"
@@ -1337,7 +1366,7 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
          "    const uint32_t per = (items + 7u) >> 3;\n"
          "    const uint32_t first = x * per;\n"
          "    const uint32_t last = (first + per < items) ? first + per : items;\n"
-         "    uint32_t item = first + j, k = 0;\n"
+         "    uint32_t item = first + j, k = k0;\n"
          "    if (item >= last) return;\n"
          "    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uni(tid >> 6);\n"
          "    const uint64_t wi = io_wave(wave);\n"
@@ -1346,39 +1375,45 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
          "    float acc[NT];\n"
          "    #pragma unroll\n"
          "    for (int i = 0; i < NT; ++i) acc[i] = 0.f;\n"
-         "    float2 nv[16];\n"
-         "    {\n"
-         "        const ReduceDesc *d0 = descs + desc_of(item);\n"
-         "        load_in(nv, ldu(&d0->psi), uni(ldu(ldu(&d0->tile_base) + row_of(item) * rt)) | wi, li);\n"
-         "    }\n"
-         "    while (true) {\n"
+      << (ahead ? "    float2 nv[16];\n"
+                  "    {\n"
+                  "        const ReduceDesc *d0 = descs + desc_of(item);\n"
+                  "        load_in(nv, ldu(&d0->psi), uni(ldu(ldu(&d0->tile_base) + (row_of(item) << rs))) | wi, li);\n"
+                  "    }\n"
+                : "")
+      << "    while (true) {\n"
          "        float2 v[16];\n"
-         "        #pragma unroll\n"
-         "        for (int r = 0; r < 16; ++r) v[r] = nv[r];\n"
-         "        const uint32_t p = desc_of(item), row = row_of(item);\n"
+      << (ahead ? "        #pragma unroll\n"
+                  "        for (int r = 0; r < 16; ++r) v[r] = nv[r];\n"
+                : "")
+      << "        const uint32_t p = desc_of(item), row = row_of(item);\n"
          "        const ReduceDesc *d = descs + p;\n"
-         "        const uint64_t base = uni(ldu(ldu(&d->tile_base) + row * rt + k));\n"
+         "        const uint64_t base = uni(ldu(ldu(&d->tile_base) + (row << rs) + (k - k0)));\n"
          "        uint32_t ni = item, nk = k + 1u;\n"
-         "        if (nk == rt) {\n"
+         "        if (nk == RT) {\n"
          "            ni = item + wpx;\n"
-         "            nk = 0u;\n"
+         "            nk = k0;\n"
          "        }\n"
          "        const bool has_next = ni < last;\n"
-         "        if (has_next) {\n"
-         "            const ReduceDesc *dn = descs + desc_of(ni);\n"
-         "            load_in(nv, ldu(&dn->psi), uni(ldu(ldu(&dn->tile_base) + row_of(ni) * rt + nk)) | wi, li);\n"
-         "        }\n"
-         "        __syncthreads();  // the previous tile's LDS and partial reads are done\n"
+      << (ahead ? "        if (has_next) {\n"
+                  "            const ReduceDesc *dn = descs + desc_of(ni);\n"
+                  "            load_in(nv, ldu(&dn->psi), uni(ldu(ldu(&dn->tile_base) + (row_of(ni) << rs) + (nk - k0))) | wi, li);\n"
+                  "        }\n"
+                : "        load_in(v, ldu(&d->psi), base | wi, li);\n")
+      << "        __syncthreads();  // the previous tile's LDS and partial reads are done\n"
          "        tile(v, tid, lane, base, lb, acc);\n"
-         "        if (by_tile) {\n"
-         "            float *ac = reinterpret_cast<float *>(ldu(&d->part)) + (uint64_t)row * (NT * T) + tid;\n"
-         "            #pragma unroll\n"
-         "            for (int i = 0; i < NT; ++i) {\n"
-         "                gout<float>(ac)[i * T] = acc[i];\n"
-         "                acc[i] = 0.f;\n"
-         "            }\n"
-         "        } else if (k == RT - 1u) {\n"
-         "            tile_flush(acc, lane, wave, red);\n"
+         "        if (k == end) {\n"
+      << (takes_by_tile(n, m)
+              ? "            if (by_tile) {\n"
+                "                float *ac = reinterpret_cast<float *>(ldu(&d->part)) + (uint64_t)row * (NT * T) + tid;\n"
+                "                #pragma unroll\n"
+                "                for (int i = 0; i < NT; ++i) {\n"
+                "                    gout<float>(ac)[i * T] = acc[i];\n"
+                "                    acc[i] = 0.f;\n"
+                "                }\n"
+                "            } else {\n"
+              : "            {\n")
+      << "            tile_flush(acc, lane, wave, red);\n"
          "            __syncthreads();\n"
          "            double *part = ldu(&d->part);\n"
          "            const uint32_t ntt = ldu(&d->n_terms_total);\n"
@@ -1386,6 +1421,7 @@ std::string jit_reduce_source(int n, int m, const TermGroup &g, const RedPlan &r
          "                double s = 0.0;\n"
          "                for (int ww = 0; ww < W; ++ww) s += red[ww * NT + c];\n"
          "                gout<double>(part)[(uint64_t)row * ntt + kCols[c]] = s;\n"
+         "            }\n"
          "            }\n"
          "        }\n"
          "        if (!has_next) break;\n"

@@ -66,6 +66,15 @@ struct JitKernel {
 // by_tile would write past its partials.
 inline int pass_mode_arg(const JitKernel &k, int remap, bool by_tile) { return k.epi ? (by_tile ? 1 : 0) : remap; }
 
+// Whether a call may ask a reducer (or a pass with an expectation epilogue) of
+// n qubits and m tile bits for single tiles: a row has several, and they may be
+// no more than there are CUs.
+constexpr uint32_t kByTileMax = 256;
+inline bool takes_by_tile(int n, int m) {
+    const uint64_t tiles = 1ull << (n - m);
+    return tiles >= kRedRowTiles && tiles <= kByTileMax;
+}
+
 // Exact structural key and source of the generated expectation reducer of
 // one term group (its terms, register phases and columns are fixed at
 // compile time; the state slot, partial-sum array and tile table are read at
