@@ -674,19 +674,18 @@ __global__ __launch_bounds__(1024) void upload_kernel(uint4 *__restrict__ dst, c
 }
 
 // ------------------------------------------------------------- init / copy
-// |0> into consecutive slots of slot_f4 (a power of two) float4. Bound by the
-// write rate: one float4 a thread and a 64-bit remainder for each took 5.4 us
-// for 8 MiB, 18.5 for 128 MiB and 339 for 2 GiB, this 4.6, 16.6 and 326.
-// THROUGH: written through the L2 (states that the next launch finds in the
-// last-level cache; no write-back at the end of the launch).
-constexpr uint32_t kInitPer = 4;   // float4 a thread writes at a time
-
-template <bool THROUGH>
+// |0> into consecutive slots of slot_f4 (a power of two) float4, PER of them a
+// thread at a time. Bound by the write rate: one float4 a thread and a 64-bit
+// remainder for each took 5.4 us for 8 MiB, 18.5 for 128 MiB, 62 for 384 MiB and
+// 375 for 2 GiB, this 4.6, 16.2, 61 and 363. THROUGH: written through the L2
+// (states that the next launch finds in the last-level cache; no write-back at
+// the end of the launch).
+template <uint32_t PER, bool THROUGH>
 __global__ __launch_bounds__(256) void init_kernel(float4 *base, uint64_t slot_f4, uint64_t total_f4) {
-    const uint64_t step = (uint64_t)gridDim.x * (256 * kInitPer);
-    for (uint64_t c = (uint64_t)blockIdx.x * (256 * kInitPer); c < total_f4; c += step) {
+    const uint64_t step = (uint64_t)gridDim.x * (256 * PER);
+    for (uint64_t c = (uint64_t)blockIdx.x * (256 * PER); c < total_f4; c += step) {
         #pragma unroll
-        for (uint32_t k = 0; k < kInitPer; ++k) {
+        for (uint32_t k = 0; k < PER; ++k) {
             const uint64_t i = c + k * 256 + threadIdx.x;
             const qw_v4u q = {(i & (slot_f4 - 1)) == 0 ? __float_as_uint(1.0f) : 0u, 0u, 0u, 0u};
             if (i < total_f4)
@@ -1644,10 +1643,16 @@ hipError_t launch_init(hipStream_t st, void *base, uint32_t n, uint32_t n_slots)
         // n == 0 is rejected by the host; keep the kernel safe anyway
         return hipErrorInvalidValue;
     }
-    const uint64_t total = slot_f4 * n_slots, per = 256 * kInitPer;
+    const uint64_t total = slot_f4 * n_slots, bytes = total * sizeof(float4);
+    if (total == 0) return hipSuccess;
+    // Up to the last-level cache's size four at a time (128 MiB 16.2 us, one at
+    // a time 16.6). Above it the write order decides: one at a time below 1 GiB
+    // (384 MiB 61, four 70; 768 MiB 128, 132) and from 4 GiB (722, 733), four in
+    // between (1 GiB 183, four 177; 1.5 GiB 270, 273; 2 GiB 375, 363).
+    const bool fits = bytes <= kIoCacheBytes, mid = bytes >= (1ull << 30) && bytes < (4ull << 30);
+    const uint64_t per = 256 * (fits || mid ? 4 : 1);
     const uint64_t blocks = std::min<uint64_t>((total + per - 1) / per, 65536);
-    if (blocks == 0) return hipSuccess;
-    auto *kernel = total * sizeof(float4) <= kIoCacheBytes ? init_kernel<true> : init_kernel<false>;
+    auto *kernel = fits ? init_kernel<4, true> : mid ? init_kernel<4, false> : init_kernel<1, true>;
     hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(256), 0, st, reinterpret_cast<float4 *>(base),
                        slot_f4, total);
     return hipGetLastError();
